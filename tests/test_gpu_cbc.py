@@ -72,3 +72,34 @@ def test_cbc_full_size_against_p2(Q):
     for c in rng.integers(1, n // 2, size=3):
         other = O.p2(n, np.concatenate([z[:-1], [c]]), threads=THREADS)
         assert other >= e2[-1] - 1e-13 * (1 + other)
+
+
+def _prime(n, step):
+    while any(n % p == 0 for p in range(2, int(n ** 0.5) + 1)):
+        n += step
+    return n
+
+
+# per transform length 2^k the smallest and the largest prime it serves
+# (n - 2 <= 2^k), and the smallest screened size
+@pytest.mark.parametrize("n,d", [(_prime(1000, 1), 6)] + [(_prime((1 << k) + 3, 1), 5) for k in range(14, 18)]
+                         + [(_prime((1 << k) + 2, -1), 5) for k in range(14, 18)]
+                         + [(_prime((1 << k) + 3, 1), 3) for k in range(18, 23)] + [(5930003, 2)])
+@pytest.mark.parametrize("weights", ["unit", "decaying", "tiny"])
+def test_cbc_screened_equals_direct(Q, n, d, weights):
+    """A prime n over the full candidate set is screened by convolution; the
+    same candidates passed as a list are all summed directly.  The vectors are
+    equal; the errors are the same sums folded in another double-double
+    order, so they differ by at most one rounding of the result (2^-53 of the
+    scale 1 + e^2, doubled for the subtraction of n).  Tiny weights make every
+    candidate a tie (the screen hands the component to the direct search)."""
+    if weights == "tiny" and n > 1 << 17:
+        pytest.skip("every component is direct there: nothing new at large n")
+    n = _prime(n, -1)
+    gam = {"unit": np.ones(d), "decaying": 1.0 / np.arange(1, d + 1) ** 2,
+           "tiny": np.array([1.0, 1e-14, 1.0, 0.0, 1.0, 1.0])[:d]}[weights]
+    _say(f"cbc screened n={n} d={d} {weights}")
+    z, e2 = Q.cbc_search(n, d, gamma=gam)
+    zd, e2d = Q.cbc_search(n, d, gamma=gam, cand=np.arange(1, n // 2 + 1, dtype=np.uint64))
+    assert list(z) == list(zd), (z, zd)
+    assert np.all(np.abs(e2 - e2d) <= 2 * 2.0 ** -53 * (1 + np.abs(e2d))), np.abs(e2 - e2d).max()
