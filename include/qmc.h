@@ -241,7 +241,8 @@ qmc_status qmc_korobov_search(uint64_t n, uint32_t d, const uint64_t *cand, uint
    (tile_points lattice points times one shift tile) ordered longest first,
    one work list per dimension, and run by one kernel launch per dimension:
    persistent workgroups that loop over the list, or one workgroup per tile
-   taking tiles in list order (schedule).  When every plan has the same d, n
+   taking tiles in list order (schedule); the dimensions' launches run on
+   parallel chains.  When every plan has the same d, n
    and m and tile_points is 0, the plans instead run as instances of one
    lattice-kernel launch (with the first plan's qmc_plan_set_launch
    configuration, if any).  When use_graph is set, the launch sequence is
@@ -269,8 +270,9 @@ typedef enum {
 typedef struct {
     int32_t use_graph;         /* capture/replay through a HIP graph */
     int32_t per_plan_launches; /* 1 = one launch per plan instead (for comparison) */
-    uint32_t tile_points;      /* lattice points per tile (0 = default 8192, or the
-                                  instance launch for uniform batches) */
+    uint32_t tile_points;      /* lattice points per tile (0 = default: 4096, fewer for
+                                  small batches, or the instance launch for uniform
+                                  batches) */
     int32_t schedule;          /* qmc_batch_schedule */
 } qmc_batch_opts;
 
@@ -367,8 +369,8 @@ qmc_status qmc_cv_train(qmc_plan_t train_plan, qmc_family family, const void *pa
    estimate of eqs. (2)-(3), as qmc_plan_create + qmc_integrate +
    qmc_plan_destroy would give it, that allocates nothing on the device.
    The rule's device copies, the parameter blob, the block partial sums and
-   the results live in a fixed 1 MiB device array inside the library (one
-   per device, held until the process ends); its address is looked up once
+   the results live in a fixed device array of about 1 MiB inside the library
+   (one per device, held until the process ends); its address is looked up once
    per device on the first call.  Limits of that array: m <= 64 shifts and a
    parameter blob of at most 8192 doubles (EUNSUPPORTED beyond).  It runs
    the precompiled kernels only (sector integrands use the table-driven

@@ -225,6 +225,64 @@ qmc_status pack_params(int family, uint32_t d, const void *params, Packed &pk) {
     return QMC_OK;
 }
 
+// The table-driven kernels' form of a sector blob (qmc_integrands.hpp):
+// coefficients of degree up to three in their Horner slots (d <= kTabMaxD), the
+// other terms and repeated monomials as coded factor lists.
+std::vector<double> table_blob(const Packed &pk, uint32_t d) {
+    if (pk.key_family != QMC_F_SECTOR && pk.key_family != kFamSectorComplex) return pk.blob;
+    const std::vector<double> &b = pk.blob;
+    auto word = [&](size_t i) {
+        uint64_t v;
+        std::memcpy(&v, &b[i], sizeof v);
+        return v;
+    };
+    const int D = (int)d, size = tab_words(D);
+    std::vector<double> out(kSectorHeader + 2 * (size_t)size, 0.0), lists;
+    std::copy(b.begin(), b.begin() + kSectorHeader, out.begin());
+    size_t at = kSectorHeader;
+    for (int w = 0; w < 2; ++w) {
+        const size_t n = word(w);
+        double *tab = out.data() + kSectorHeader + (size_t)w * size;
+        std::vector<uint32_t> mask(size, 0u);
+        std::vector<char> used(size, 0);
+        std::vector<double> coef, code;
+        for (size_t t = 0; t < n; ++t) {
+            const double c = b[at + t];
+            const uint64_t m = word(at + n + t);
+            const uint32_t cnt = (uint32_t)(m & 15u);
+            // factors ascend (monomial_code)
+            const int v0 = (int)((m >> 4) & 31u), v1 = (int)((m >> 9) & 31u), v2 = (int)((m >> 14) & 31u);
+            if (D > kTabMaxD) {
+                coef.push_back(c);
+                code.push_back(bits(m));
+                continue;
+            }
+            const int slot = cnt == 0   ? 0
+                             : cnt == 1 ? tab_a_off(D, v0)
+                             : cnt == 2 ? tab_pair_off(D, v0, v1)
+                                        : tab_pair_off(D, v0, v1) + 2 + v2 - v1;
+            if (cnt > 3 || used[slot]) {
+                coef.push_back(c);
+                code.push_back(bits(m));
+                continue;
+            }
+            used[slot] = 1;
+            tab[slot] = c;
+            if (cnt >= 1) mask[tab_a_off(D, v0) + 1] |= kTabPresent;
+            if (cnt >= 2) mask[tab_a_off(D, v0) + 1] |= 1u << v1;
+            if (cnt == 3) mask[tab_pair_off(D, v0, v1) + 1] |= 1u << v2;
+        }
+        for (int i = 0; i < size; ++i)
+            if (mask[i]) tab[i] = bits(mask[i]);
+        out[w] = bits(coef.size());
+        lists.insert(lists.end(), coef.begin(), coef.end());
+        lists.insert(lists.end(), code.begin(), code.end());
+        at += 2 * n;
+    }
+    out.insert(out.end(), lists.begin(), lists.end());
+    return out;
+}
+
 double transform_scale(const qmc_transform &t, uint32_t d) {
     if (t.kind == QMC_T_SIDI) {
         // 1 / T_m per dimension, T_m = int_0^1 sin^m(pi x) dx
@@ -323,23 +381,23 @@ std::vector<double> padded_shifts(const std::vector<double> &sh, uint32_t m, uin
 }
 
 // --------------------------------------------------------------- plan ops
-qmc_status plan_upload_params(qmc_plan_s *p, const Packed &pk) {
-    if (pk.blob.size() > p->params_cap) {
+qmc_status plan_upload_params(qmc_plan_s *p, const std::vector<double> &blob) {
+    if (blob.size() > p->params_cap) {
         if (p->d_params) hipFree(p->d_params);
         p->d_params = nullptr;
         p->params_cap = 0;
-        hipError_t e = hipMalloc(&p->d_params, pk.blob.size() * sizeof(double));
+        hipError_t e = hipMalloc(&p->d_params, blob.size() * sizeof(double));
         if (e != hipSuccess) return fail(QMC_ENOMEM, "hipMalloc params: %s", hipGetErrorString(e));
-        p->params_cap = pk.blob.size();
+        p->params_cap = blob.size();
         p->last_blob.clear();
     }
-    if (pk.blob != p->last_blob) {
-        hipError_t e = hipMemcpyAsync(p->d_params, pk.blob.data(), pk.blob.size() * sizeof(double),
+    if (blob != p->last_blob) {
+        hipError_t e = hipMemcpyAsync(p->d_params, blob.data(), blob.size() * sizeof(double),
                                       hipMemcpyHostToDevice, p->stream);
         if (e != hipSuccess) return hip_fail(e, "upload params");
         e = hipStreamSynchronize(p->stream);
         if (e != hipSuccess) return hip_fail(e, "upload params");
-        p->last_blob = pk.blob;
+        p->last_blob = blob;
     }
     return QMC_OK;
 }
@@ -372,7 +430,7 @@ qmc_status plan_set_gstep(qmc_plan_s *p, uint32_t S) {
 static qmc_status plan_launch(qmc_plan_s *p, const Packed &pk, LatticeLaunch fn, hipFunction_t jfn, uint32_t T,
                               uint32_t bpc) {
     if (p->m * pk.np > kMaxRows) return fail(QMC_EUNSUPPORTED, "m * parts > %u", kMaxRows);
-    qmc_status st = plan_upload_params(p, pk);
+    qmc_status st = jfn ? plan_upload_params(p, pk.blob) : plan_upload_params(p, table_blob(pk, p->d));
     if (st) return st;
     const uint32_t tiles = (p->m + T - 1) / T;
     const uint32_t bx = grid_x(p->n, tiles, p->device, bpc);

@@ -1869,7 +1869,7 @@ qmc_status qmc_cv_train(qmc_plan_t p, qmc_family family, const void *params, uin
     if (pk.deform) return fail(QMC_EUNSUPPORTED, "control variates take undeformed sectors (deform_lambda = 0)");
     hipFunction_t sample = jit_sample_kernel(pk.blob, d, p->tr, pk.cplx, p->device, err);
     if (!sample) return fail(QMC_EUNSUPPORTED, "training sampler: %s", err.c_str());
-    if ((st = plan_upload_params(p, pk))) return st;
+    if ((st = plan_upload_params(p, pk.blob))) return st;
 
     CvTrainer t;
     if ((st = t.init(n, d, R, K, true, true))) return st;
@@ -1992,7 +1992,7 @@ qmc_status qmc_cv_samples(qmc_plan_t p, qmc_family family, const void *params, u
     std::string err;
     hipFunction_t sample = jit_sample_kernel(pk.blob, p->d, p->tr, pk.cplx, p->device, err);
     if (!sample) return fail(QMC_EUNSUPPORTED, "training sampler: %s", err.c_str());
-    if ((st = plan_upload_params(p, pk))) return st;
+    if ((st = plan_upload_params(p, pk.blob))) return st;
     const uint32_t n = p->n, d = p->d, blocks = (n + kBlock - 1) / kBlock;
     DeviceScratch s;
     if ((st = s.alloc((size_t)n * d * 4)) || (st = s.alloc((size_t)n * 4)) || (st = s.alloc((size_t)n * 4)))

@@ -416,13 +416,120 @@ struct FamGenzCornerPeak {
 };
 
 // ---------------------------------------------------- sparse polynomials
-// A monomial is coded as a 64-bit word: bits 0..3 hold the number of
-// factors c (<= 12), bits 4+5f..8+5f the variable of factor f; z_i^2 is two
-// factors of variable i.  The code and the coefficient are wave-uniform, so
-// the factor loop and the variable selection below become scalar branches;
-// only the multiplications run on the vector unit, once per shift.
+// The table-driven form of a polynomial is its nested Horner scheme over
+// sorted variables,
+//   P = c + sum_a z_a (c_a + sum_{b >= a} z_b (c_ab + sum_{c >= b} c_abc z_c)),
+// with one fixed slot per coefficient (c_0; per a: c_a and the mask of its
+// b; per (a, b): c_ab, the mask of its c, and the D - b slots c_abc).  The
+// loops over a, b, c are unrolled, so every variable is a register known at
+// compile time and the masks only decide which steps are skipped: one scalar
+// bit test and branch per possible step (a pair block's coefficients come
+// with one group of scalar loads), one FMA per term and shift.  A term read as
+// a coded factor list (a chain of scalar branches per factor to find its
+// variable, and a multiply per factor) is bound by scalar issue.  100 sectors
+// of d = 2 .. 9 at n = 262139, m = 16, four shifts per thread, in a batch: 3.1 ms
+// (1.3e11 evaluations/s) against 16.2 ms with every term listed.
+// Monomials of degree above three, and repeated ones, stay in a list of
+// coded factors: bits 0..3 of a code hold the number of factors (<= 12), bits
+// 4+5f..8+5f the variable of factor f; z_i^2 is two factors of variable i.
+// So do all terms beyond kTabMaxD dimensions: the unrolled code grows with
+// d^3 (21, 33 and 52 KB at d = 9, 12, 16 with four shifts), and past 12 it
+// neither shares an instruction cache of 64 KB with the rest of the kernel nor
+// leaves two waves per SIMD.
+constexpr int kTabMaxD = 12;
+constexpr uint32_t kTabPresent = 1u << 31;  // in an a-mask: some term starts with z_a
+constexpr int tab_pair_words(int d, int b) { return 2 + d - b; }
+constexpr int tab_a_off(int d, int a) {  // words before the block of a (tab_a_off(d, d): table size)
+    int o = 1;
+    for (int i = 0; i < a; ++i) {
+        o += 2;
+        for (int b = i; b < d; ++b) o += tab_pair_words(d, b);
+    }
+    return o;
+}
+constexpr int tab_pair_off(int d, int a, int b) {
+    int o = tab_a_off(d, a) + 2;
+    for (int i = a; i < b; ++i) o += tab_pair_words(d, i);
+    return o;
+}
+
+constexpr int tab_words(int d) { return d <= kTabMaxD ? tab_a_off(d, d) : 0; }
+
+// parameter words behind a uniform address, read with scalar loads
+typedef const __attribute__((address_space(4))) double *scalar_ptr;
+__device__ __forceinline__ scalar_ptr scalar_words(const double *p) {
+    scalar_ptr q = (scalar_ptr)uniform_ptr(p);
+    asm volatile("" : "+s"(q));  // keep the loads where they are written
+    return q;
+}
+__device__ __forceinline__ uint32_t scalar_u32(scalar_ptr q) {
+    return *(const __attribute__((address_space(4))) uint32_t *)q;
+}
+
+// f(i) for i = LO .. HI - 1 as compile-time constants (index_const<i>); the
+// loops of poly_table are too deep for the loop unroller
+template <int I>
+struct index_const {
+    static constexpr int value = I;
+};
+template <int LO, int HI, class Fn>
+__device__ __forceinline__ void static_for(Fn &&f) {
+    if constexpr (LO < HI) {
+        f(index_const<LO>{});
+        static_for<LO + 1, HI>(f);
+    }
+}
+
+template <int D, int T>
+__device__ __forceinline__ void poly_table(const double *tab, const double (&z)[T][D], double (&out)[T]) {
+    const scalar_ptr t = scalar_words(tab);
+    {
+        const double c0 = t[0];
+#pragma unroll
+        for (int k = 0; k < T; ++k) out[k] = c0;
+    }
+    static_for<0, D>([&](auto ia) {
+        constexpr int a = decltype(ia)::value, ao = tab_a_off(D, a);
+        const uint32_t am = scalar_u32(t + ao + 1);
+        if (am & kTabPresent) {
+            double A[T];
+            const double ca = t[ao];
+#pragma unroll
+            for (int k = 0; k < T; ++k) A[k] = ca;
+            static_for<a, D>([&](auto ib) {
+                constexpr int b = decltype(ib)::value, po = tab_pair_off(D, a, b);
+                if (am & (1u << b)) {
+                    const uint32_t cm = scalar_u32(t + po + 1);
+                    const double cab = t[po];
+                    double cc[D - b];
+#pragma unroll
+                    for (int c = 0; c < D - b; ++c) {
+                        cc[c] = t[po + 2 + c];
+                        asm volatile("" : "+s"(cc[c]));  // loaded here, not behind each branch
+                    }
+                    double B[T];
+#pragma unroll
+                    for (int k = 0; k < T; ++k) B[k] = cab;
+                    static_for<b, D>([&](auto ic) {
+                        constexpr int c = decltype(ic)::value;
+                        if (cm & (1u << c)) {
+                            asm volatile("");  // a branch, not four selects
+#pragma unroll
+                            for (int k = 0; k < T; ++k) B[k] = fma_(z[k][c], cc[c - b], B[k]);
+                        }
+                    });
+#pragma unroll
+                    for (int k = 0; k < T; ++k) A[k] = fma_(z[k][b], B[k], A[k]);
+                }
+            });
+#pragma unroll
+            for (int k = 0; k < T; ++k) out[k] = fma_(z[k][a], A[k], out[k]);
+        }
+    });
+}
+
 // Runs f(i) for the one variable i = v in [LO, HI), choosing it by halving
-// the range: ceil(log2 D) uniform branches instead of one test per variable.
+// the range: ceil(log2 D) uniform branches.
 template <int LO, int HI, int D, int T, class Fn>
 __device__ __forceinline__ void pick_var(uint32_t v, Fn &&f) {
     if constexpr (HI - LO == 1) {
@@ -436,46 +543,23 @@ __device__ __forceinline__ void pick_var(uint32_t v, Fn &&f) {
     }
 }
 
+// out[k] += sum_t coef[t] * prod_f z[k][var_f(t)] over the listed terms
 template <int D, int T>
-__device__ __forceinline__ void mul_var(double (&q)[T], const double (&z)[T][D], uint32_t v) {
-    pick_var<0, D, D, T>(v, [&](int i) {
-#pragma unroll
-        for (int k = 0; k < T; ++k) q[k] *= z[k][i];
-    });
-}
-
-template <int D, int T>
-__device__ __forceinline__ void scale_var(double (&q)[T], double c, const double (&z)[T][D],
-                                          uint32_t v) {
-    pick_var<0, D, D, T>(v, [&](int i) {
-#pragma unroll
-        for (int k = 0; k < T; ++k) q[k] = c * z[k][i];
-    });
-}
-
-// out[k] = sum_t coef[t] * prod_f z[k][var_f(t)]
-template <int D, int T>
-__device__ __forceinline__ void poly_eval(const double *__restrict__ coef,
-                                          const uint64_t *__restrict__ code, uint32_t nt,
-                                          const double (&z)[T][D], double (&out)[T]) {
-#pragma unroll
-    for (int k = 0; k < T; ++k) out[k] = 0.0;
+__device__ __forceinline__ void poly_list(const double *__restrict__ coef, const uint64_t *__restrict__ code,
+                                          uint32_t nt, const double (&z)[T][D], double (&out)[T]) {
     for (uint32_t t = 0; t < nt; ++t) {
         uint64_t c = code[t];
         const double cf = coef[t];
         const uint32_t cnt = (uint32_t)(c & 15u);
-        if (cnt == 0) {
-#pragma unroll
-            for (int k = 0; k < T; ++k) out[k] += cf;
-            continue;
-        }
         c >>= 4;
         double q[T];
-        scale_var<D, T>(q, cf, z, (uint32_t)(c & 31u));
-        for (uint32_t f = 1; f < cnt; ++f) {
-            c >>= 5;
-            mul_var<D, T>(q, z, (uint32_t)(c & 31u));
-        }
+#pragma unroll
+        for (int k = 0; k < T; ++k) q[k] = cf;
+        for (uint32_t f = 0; f < cnt; ++f, c >>= 5)
+            pick_var<0, D, D, T>((uint32_t)(c & 31u), [&](int i) {
+#pragma unroll
+                for (int k = 0; k < T; ++k) q[k] *= z[k][i];
+            });
 #pragma unroll
         for (int k = 0; k < T; ++k) out[k] += q[k];
     }
@@ -506,6 +590,10 @@ __device__ __forceinline__ void nu_eval(uint32_t code, const double (&init)[T], 
 // with the two Symanzik-type polynomials; -i delta as in eq. (7)).
 // blob: [n_u, n_f, flags, pow_u, pow_f, delta, nu (2 bits per variable),
 //        coef_u (n_u), code_u (n_u), coef_f (n_f), code_f (n_f)]
+// (the specialised functors').  The table-driven functor reads
+//       [l_u, l_f, flags, pow_u, pow_f, delta, nu,
+//        table of U, table of F (tab_words(d) words each),
+//        listed terms: coef_u (l_u), code_u (l_u), coef_f (l_f), code_f (l_f)]
 // flags bit 0: complex, bit 1: pow_u == -2 (U^-2 by reciprocal).
 enum : uint32_t { kSectorComplex = 1u, kSectorPowUm2 = 2u };
 // Expansion orders (qmc_integrate_orders, flag 4): three words after the F
@@ -699,18 +787,30 @@ struct FamSector {
                                 double (&v)[T][NP]) {
         double z[T][D], jac[T];
         apply_transform<Tr, D, T>(x, z, jac);
-        const uint32_t nu = (uint32_t)__double_as_longlong(p[0]);
-        const uint32_t nf = (uint32_t)__double_as_longlong(p[1]);
+        const uint32_t lu = (uint32_t)__double_as_longlong(p[0]);
+        const uint32_t lf = (uint32_t)__double_as_longlong(p[1]);
         const uint32_t flags = (uint32_t)__double_as_longlong(p[2]);
         const double pow_u = p[3], pow_f = p[4], delta = p[5];
         const uint32_t nucode = (uint32_t)__double_as_longlong(p[6]);
-        const double *cu = p + kSectorHeader;
-        const uint64_t *eu = reinterpret_cast<const uint64_t *>(cu + nu);
-        const double *cf = cu + 2 * nu;
-        const uint64_t *ef = reinterpret_cast<const uint64_t *>(cf + nf);
-        double U[T], F[T], mono[T];
-        poly_eval<D, T>(cu, eu, nu, z, U);
-        poly_eval<D, T>(cf, ef, nf, z, F);
+        constexpr int kTab = tab_words(D);
+        double U[T], F[T] = {}, mono[T];
+        if constexpr (D <= kTabMaxD) {
+            // U, then F, by the same code (unrolled over the variables it is large)
+#pragma unroll 1
+            for (int w = 0; w < 2; ++w) {
+#pragma unroll
+                for (int k = 0; k < T; ++k) U[k] = F[k];
+                poly_table<D, T>(p + kSectorHeader + w * kTab, z, F);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < T; ++k) U[k] = 0.0;
+        }
+        if (lu | lf) {
+            const double *lu_c = p + kSectorHeader + 2 * kTab, *lf_c = lu_c + 2 * lu;
+            poly_list<D, T>(lu_c, reinterpret_cast<const uint64_t *>(lu_c + lu), lu, z, U);
+            poly_list<D, T>(lf_c, reinterpret_cast<const uint64_t *>(lf_c + lf), lf, z, F);
+        }
         nu_eval<D, T>(nucode, jac, z, mono);
 #pragma unroll
         for (int k = 0; k < T; ++k) sector_finish<Complex>(mono[k], U[k], F[k], flags, pow_u, pow_f, delta, v[k]);

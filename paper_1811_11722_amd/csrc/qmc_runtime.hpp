@@ -84,7 +84,8 @@ uint32_t default_tile(int key_family);
 uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu);
 void gstep_for(const uint32_t *g, uint32_t d, uint32_t n, uint64_t S, uint32_t *out);
 qmc_status ensure_buffer(void **ptr, size_t &cap, size_t bytes, const char *what);
-qmc_status plan_upload_params(qmc_plan_s *p, const Packed &pk);
+qmc_status plan_upload_params(qmc_plan_s *p, const std::vector<double> &blob);
+std::vector<double> table_blob(const Packed &pk, uint32_t d);
 qmc_status plan_set_gstep(qmc_plan_s *p, uint32_t S);
 qmc_status plan_enqueue(qmc_plan_s *p, const Packed &pk, uint32_t want_T, uint32_t blocks_per_cu);
 qmc_status plan_collect(qmc_plan_s *p, uint32_t np, qmc_result *out, double *per_shift, bool crossing = false);

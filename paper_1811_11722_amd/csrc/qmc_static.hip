@@ -17,7 +17,9 @@
 
 namespace qmc {
 
-constexpr size_t kScratchBytes = size_t(1) << 20;
+// the tables a sector's blob grows by in the table-driven kernels' form
+constexpr size_t kStaticTables = (2 * (size_t)tab_words(kTabMaxD) * 8 + 255) / 256 * 256;
+constexpr size_t kScratchBytes = (size_t(1) << 20) + kStaticTables;
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -32,7 +34,7 @@ constexpr size_t kOffShifts = 512;                                    // <= 64 r
 constexpr size_t kOffOut = kOffShifts + (size_t)kStaticMaxM * kMaxDim * 8;
 constexpr size_t kOutBytes = ((kMaxParts * kStaticMaxM + 2 * kMaxParts) * 8 + 255) / 256 * 256;
 constexpr size_t kOffBlob = kOffOut + kOutBytes;
-constexpr size_t kOffPartials = kOffBlob + kStaticMaxBlob * 8;
+constexpr size_t kOffPartials = kOffBlob + kStaticMaxBlob * 8 + kStaticTables;
 static_assert(kOffPartials % 256 == 0, "aligned regions");
 static_assert(kOffPartials < kScratchBytes, "scratch too small");
 
@@ -98,6 +100,8 @@ extern "C" qmc_status qmc_integrate_static(uint32_t d, uint64_t n, const uint64_
     const uint32_t rows = padded_rows(m);
     const std::vector<double> sh = padded_shifts(std::vector<double>(shifts, shifts + (size_t)m * d), m, d, rows, t);
 
+    const std::vector<double> blob = table_blob(pk, d);
+
     hipStream_t s = (hipStream_t)stream;
     uint32_t *d_g = reinterpret_cast<uint32_t *>(base + kOffG);
     uint32_t *d_gs = reinterpret_cast<uint32_t *>(base + kOffGstep);
@@ -108,7 +112,7 @@ extern "C" qmc_status qmc_integrate_static(uint32_t d, uint64_t n, const uint64_
     if ((e = hipMemcpyAsync(d_g, g32, d * 4, hipMemcpyHostToDevice, s)) != hipSuccess ||
         (e = hipMemcpyAsync(d_gs, gs, d * 4, hipMemcpyHostToDevice, s)) != hipSuccess ||
         (e = hipMemcpyAsync(d_sh, sh.data(), sh.size() * 8, hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(d_blob, pk.blob.data(), pk.blob.size() * 8, hipMemcpyHostToDevice, s)) != hipSuccess)
+        (e = hipMemcpyAsync(d_blob, blob.data(), blob.size() * 8, hipMemcpyHostToDevice, s)) != hipSuccess)
         return hip_fail(e, "static upload");
 
     LatticeArgs a{};

@@ -447,6 +447,42 @@ def test_sector_complex(Q, launch, jit):
     complex_sector_check(q, n, g, sh, tab, label=f"launch={launch} jit={jit}")
 
 
+@pytest.mark.parametrize("d", [1, 2, 3, 11, 12, 13, 16])
+@pytest.mark.parametrize("batch", [False, True])
+def test_sector_table_forms(Q, d, batch):
+    """The table-driven polynomial at its edges: one variable, the last
+    dimension with coefficient tables and the first without, degree one to
+    three in sorted slots, degree four to twelve and repeated monomials in the
+    factor list, zero coefficients, constants only.  Every value is a sum of
+    positive terms, a few tens of roundings from the oracle's: 1e-12 as above."""
+    n, m = 1021, 5
+    if batch and d > 12:
+        pytest.skip("the batch kernels end at d = 12")
+    rng = np.random.default_rng(900 + d)
+    unit = lambda *v: [sum(1 for x in v if x % d == i) for i in range(d)]
+    rows = [[0] * d, unit(0), unit(d - 1), unit(0, d - 1), unit(d // 2, d - 1)]
+    if d >= 3:
+        rows += [unit(0, 1, 2), unit(0, d - 1, d - 1), unit(d - 2, d - 2, d - 1), unit(0, 1, d - 2, d - 1)]
+    if d >= 6:
+        rows += [[2] * 6 + [0] * (d - 6), [1] * d if d <= 12 else [1] * 12 + [0] * (d - 12)]
+    rows += [rows[1], rows[-1], rows[3]]  # repeated
+    exp_f = np.minimum(np.array(rows, np.uint8), 2)
+    coef_f = 10.0 ** rng.uniform(-1, 1, len(rows))
+    coef_f[2] = 0.0
+    tab = synth.SectorTables(d=d, coef_u=np.array([1.5, 0.25]), exp_u=np.zeros((2, d), np.uint8), coef_f=coef_f,
+                             exp_f=exp_f, nu=np.array([i % 3 for i in range(d)], np.uint8))
+    g, sh = O.korobov_vector(n, d, 76), synth.shifts(900 + d, m, d)
+    _say(f"sector table forms d={d} batch={batch}")
+    if batch:
+        plans = [Q.Plan(d, k, O.korobov_vector(k, d, 76), sh, "baker") for k in (n, 257)]
+        Q.integrate_batch(plans, [Q.Params("sector", d, sector=tab)] * 2)
+        q = Q.batch_per_shift(plans)[0]
+        est = O.estimate(n, g, sh, O.Params("sector", d, sector=tab), "baker", 0, threads=THREADS)
+    else:
+        _, q, est = _both(Q, "sector", d, n, g, sh, "baker", jit=0, sector=tab)
+    assert np.all(_rel(q, est.q_re) < TOL), _rel(q, est.q_re).max()
+
+
 def test_xmy_toy_integral(Q):
     """eq. (7) as a complex sector: U = 1, F = x1 - x2, delta = 1e-2."""
     d, n, m = 2, 65521, 8
