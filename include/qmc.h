@@ -254,7 +254,7 @@ typedef enum {
     QMC_BATCH_PERSISTENT = 1, /* CUs x 8 workgroups loop over the work list */
     QMC_BATCH_PER_TILE = 2,   /* one workgroup per tile */
     /* sectors only: one launch per plan of the run-time specialised sector
-       kernel (with use_graph: every plan's kernel, finalize and result copy
+       kernel (with use_graph: every plan's kernel and finalize
        captured into one HIP graph on four parallel chains and replayed by
        later calls with the same plans, exponent structures and buffers; the
        coefficients are uploaded before each replay).  Each distinct exponent

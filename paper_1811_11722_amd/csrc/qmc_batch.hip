@@ -60,12 +60,12 @@ struct BatchCtx {
     LatticeArgs largs{};
     FinalizeArgs lfargs{};
     uint32_t lbx = 0, ltiles = 0;
-    DeviceScratch dev;  // sectors, tiles, g, gstep, shifts, params, counter, partials, q, res
+    DeviceScratch dev;  // sectors, tiles, g, gstep, shifts, params, counter, partials
     BatchArgs args{};
     FinalizeBatchArgs fargs{};
     std::vector<BatchSector> hs;
     size_t nq = 0;
-    double *h_q = nullptr, *h_res = nullptr;
+    double *h_q = nullptr, *h_res = nullptr;  // pinned; written by the finalize kernel
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     uint32_t blocks = 0;
@@ -156,8 +156,7 @@ qmc_status build_uniform(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, c
     qmc_status st;
     if ((st = c.dev.alloc(g.size() * 4)) || (st = c.dev.alloc(gs.size() * 4)) || (st = c.dev.alloc(sh.size() * 8)) ||
         (st = c.dev.alloc(prm.size() * 8)) ||
-        (st = c.dev.alloc((size_t)count * m * c.np * c.lbx * sizeof(double2))) || (st = c.dev.alloc(c.nq * 8)) ||
-        (st = c.dev.alloc((size_t)count * 32)))
+        (st = c.dev.alloc((size_t)count * m * c.np * c.lbx * sizeof(double2))))
         return st;
     hipError_t e;
     if ((e = hipMemcpy(c.dev.ptr[0], g.data(), g.size() * 4, hipMemcpyHostToDevice)) != hipSuccess ||
@@ -193,10 +192,8 @@ qmc_status build_uniform(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, c
     f.n = (double)n;
     f.scale = transform_scale(p0->tr, d);
     f.sub = 0.0;
-    f.q = (double *)c.dev.ptr[5];
-    f.res = (double *)c.dev.ptr[6];
-    c.fargs.q = f.q;
-    c.fargs.res = f.res;
+    f.q = c.h_q;
+    f.res = c.h_res;
     return QMC_OK;
 }
 
@@ -316,8 +313,7 @@ qmc_status build_ctx(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, const
     if ((st = c.dev.alloc(c.hs.size() * sizeof(BatchSector))) || (st = c.dev.alloc(tiles.size() * sizeof(BatchTile))) ||
         (st = c.dev.alloc(g.size() * 4)) || (st = c.dev.alloc(gs.size() * 4)) || (st = c.dev.alloc(sh.size() * 8)) ||
         (st = c.dev.alloc(prm.size() * 8)) || (st = c.dev.alloc(4 * c.groups.size() + 64)) ||
-        (st = c.dev.alloc(psize)) ||
-        (st = c.dev.alloc(qoff * 8)) || (st = c.dev.alloc((size_t)count * 32)))
+        (st = c.dev.alloc(psize)))
         return st;
     hipError_t e;
     auto up = [&](int k, const void *src, size_t bytes) {
@@ -347,8 +343,8 @@ qmc_status build_ctx(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, const
     c.fargs.partials = c.args.partials;
     c.fargs.T = T;
     c.fargs.np = c.np;
-    c.fargs.q = (double *)c.dev.ptr[8];
-    c.fargs.res = (double *)c.dev.ptr[9];
+    c.fargs.q = c.h_q;
+    c.fargs.res = c.h_res;
     c.blocks = (uint32_t)device_cu_count(c.device) * 8;
     const size_t sides = std::min(kBatchChains, c.groups.size()) - 1;
     if (sides && (e = hipEventCreateWithFlags(&c.fork, hipEventDisableTiming)) != hipSuccess)
@@ -465,8 +461,8 @@ static qmc_status spec_prepare(qmc_plan_s *p, const Packed &pk, SpecPlan &sp) {
     return st;
 }
 
-// lattice kernel, finalize kernel and the copy of the results to the
-// plan's pinned mirror, on stream s
+// lattice kernel and finalize kernel (which writes the plan's pinned result
+// buffer), on stream s
 static hipError_t spec_enqueue(qmc_plan_s *p, const Packed &pk, const SpecPlan &sp, hipStream_t s) {
     LatticeArgs a{};
     a.n = p->n;
@@ -491,10 +487,9 @@ static hipError_t spec_enqueue(qmc_plan_s *p, const Packed &pk, const SpecPlan &
     f.n = (double)p->n;
     f.scale = transform_scale(p->tr, p->d);
     f.sub = 0.0;
-    f.q = p->d_out;
-    f.res = p->d_out + out_res_offset(p->m);
-    if ((e = launch_finalize(f, 1, s)) != hipSuccess) return e;
-    return hipMemcpyAsync(p->h_out, p->d_out, out_doubles(p->m) * sizeof(double), hipMemcpyDeviceToHost, s);
+    f.q = p->h_out;
+    f.res = p->h_out + out_res_offset(p->m);
+    return launch_finalize(f, 1, s);
 }
 
 // A captured specialised schedule: the kernels of every plan on kSpecChains
@@ -504,7 +499,7 @@ constexpr int kSpecChains = 4;
 struct SpecCtx {
     std::vector<qmc_plan_s *> plans;
     std::vector<SpecPlan> sp;
-    std::vector<std::vector<const void *>> bufs;  // per plan: params, partials, out, gstep, g, shifts, h_out
+    std::vector<std::vector<const void *>> bufs;  // per plan: params, partials, gstep, g, shifts, h_out
     hipStream_t stream = nullptr;
     hipStream_t side[kSpecChains] = {};
     hipEvent_t fork = nullptr, join[kSpecChains] = {};
@@ -525,7 +520,7 @@ struct SpecCtx {
 std::vector<std::unique_ptr<SpecCtx>> g_spec;
 
 static std::vector<const void *> spec_buffers(qmc_plan_s *p) {
-    return {p->d_params, p->d_partials, p->d_out, p->d_gstep, p->d_g, p->d_shifts, p->h_out};
+    return {p->d_params, p->d_partials, p->d_gstep, p->d_g, p->d_shifts, p->h_out};
 }
 
 static qmc_status spec_capture(SpecCtx &c, const std::vector<Packed> &pk) {
@@ -696,9 +691,6 @@ qmc_status qmc_integrate_batch(uint32_t count, const qmc_plan_t *plans, qmc_fami
             p->stream = c->stream;
             p->jit_mode = 0;
             qmc_status st = plan_enqueue(p, pk[i], c->T, 0);
-            if (!st && (e = hipMemcpyAsync(p->h_out, p->d_out, out_doubles(p->m) * sizeof(double),
-                                           hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
-                st = hip_fail(e, "copy results");
             p->stream = keep;
             p->jit_mode = jit;
             if (st) return st;
@@ -725,11 +717,7 @@ qmc_status qmc_integrate_batch(uint32_t count, const qmc_plan_t *plans, qmc_fami
         qmc_status st = run_graph(*c, o.use_graph != 0);
         if (st) return st;
         if (p0->timing) (void)hipEventRecord(p0->ev1, c->stream);
-        if ((e = hipMemcpyAsync(c->h_q, c->fargs.q, c->nq * 8, hipMemcpyDeviceToHost, c->stream)) != hipSuccess ||
-            (e = hipMemcpyAsync(c->h_res, c->fargs.res, (size_t)count * 32, hipMemcpyDeviceToHost, c->stream)) !=
-                hipSuccess ||
-            (e = hipStreamSynchronize(c->stream)) != hipSuccess)
-            return hip_fail(e, "batch results");
+        if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return hip_fail(e, "batch results");
         if (p0->timing) {
             float ms = 0.f;
             if (hipEventElapsedTime(&ms, p0->ev0, p0->ev1) == hipSuccess) {

@@ -4,9 +4,9 @@
 // shifts and the periodising transform -- resident in device memory.  Each
 // qmc_integrate call packs the integrand parameters into a blob (uploaded
 // only when it changed), launches the lattice kernel and the finalize kernel
-// on the plan's stream and copies back the m per-shift values and the
-// (mean, error) of eqs. (2)-(3): one small host->device copy at most and
-// one device->host copy per estimate.
+// on the plan's stream, which writes the m per-shift values and the
+// (mean, error) of eqs. (2)-(3) to the plan's pinned memory: one small
+// host->device copy at most per estimate and no copy back.
 #include "qmc_runtime.hpp"
 
 #include <algorithm>
@@ -343,18 +343,21 @@ uint32_t default_tile(int key_family) {
 }
 
 // Workgroups along the points: about blocks_per_cu (default 8) per CU over
-// all shift tiles, and at most one per kBlock x kMinPointsPerThread points.
-// Below that floor a thread would walk one or two points and the launch
-// would be all block reductions and partials (one instance of n = 131071,
-// m = 16: 17.4 us -> 13.2 us per kernel with the floor).
+// all shift tiles, and at most one per kBlock x kMinPointsPerThread points
+// once every CU has one.  Below that floor a thread would walk one or two
+// points and the launch would be all block reductions and partials (one
+// instance of n = 131071, m = 16: 17.4 us -> 13.2 us per kernel with the
+// floor); with fewer workgroups than CUs the walk's length is what the launch
+// waits for, down to one point per thread (n = 16381, m = 16, d = 6 sector: 11.1
+// -> 7.0 us per kernel).
 constexpr uint64_t kMinPointsPerThread = 4;
 
 uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu) {
-    const uint64_t target = (uint64_t)device_cu_count(dev) * (blocks_per_cu ? blocks_per_cu : 8);
-    uint64_t bx = std::max<uint64_t>(1, target / std::max<uint32_t>(1, tiles_total));
-    const uint64_t cap = (n + kBlock * kMinPointsPerThread - 1) / (kBlock * kMinPointsPerThread);
-    bx = std::min(bx, cap);
-    return (uint32_t)std::max<uint64_t>(bx, 1);
+    const uint64_t cus = (uint64_t)device_cu_count(dev), tiles = std::max<uint32_t>(1, tiles_total);
+    const uint64_t bx = std::max<uint64_t>(1, cus * (blocks_per_cu ? blocks_per_cu : 8) / tiles);
+    auto groups = [n](uint64_t per) { return (n + kBlock * per - 1) / (kBlock * per); };
+    const uint64_t cap = std::max(groups(kMinPointsPerThread), std::min(groups(1), cus / tiles));
+    return (uint32_t)std::max<uint64_t>(std::min(bx, cap), 1);
 }
 
 void gstep_for(const uint32_t *g, uint32_t d, uint32_t n, uint64_t S, uint32_t *out) {
@@ -464,8 +467,8 @@ static qmc_status plan_launch(qmc_plan_s *p, const Packed &pk, LatticeLaunch fn,
     f.n = (double)p->n;
     f.scale = transform_scale(p->tr, p->d);
     f.sub = 0.0;
-    f.q = p->d_out;
-    f.res = p->d_out + out_res_offset(p->m);
+    f.q = p->h_out;
+    f.res = p->h_out + out_res_offset(p->m);
     e = launch_finalize(f, 1, p->stream);
     if (e != hipSuccess) return hip_fail(e, "launch finalize kernel");
     p->last_T = T;
@@ -514,10 +517,7 @@ qmc_status plan_enqueue(qmc_plan_s *p, const Packed &pk, uint32_t want_T, uint32
 }
 
 qmc_status plan_collect(qmc_plan_s *p, uint32_t np, qmc_result *out, double *per_shift, bool crossing) {
-    hipError_t e = hipMemcpyAsync(p->h_out, p->d_out, out_doubles(p->m) * sizeof(double), hipMemcpyDeviceToHost,
-                                  p->stream);
-    if (e != hipSuccess) return hip_fail(e, "copy results");
-    e = hipStreamSynchronize(p->stream);
+    hipError_t e = hipStreamSynchronize(p->stream);
     if (e != hipSuccess) return hip_fail(e, "synchronize");
     if (p->timing) {
         float ms = 0.f;
@@ -642,8 +642,7 @@ qmc_status qmc_plan_create(uint32_t d, uint64_t n, const uint64_t *g, uint32_t m
     if ((st = ensure_buffer((void **)&p->d_g, cap, d * sizeof(uint32_t), "g")) ||
         (cap = 0, st = ensure_buffer((void **)&p->d_gstep, cap, d * sizeof(uint32_t), "gstep")) ||
         (cap = 0, st = ensure_buffer((void **)&p->d_shifts, cap, (size_t)padded_rows(m) * d * sizeof(double),
-                                     "shifts")) ||
-        (cap = 0, st = ensure_buffer((void **)&p->d_out, cap, out_doubles(m) * sizeof(double), "out"))) {
+                                     "shifts"))) {
         qmc_plan_destroy(p);
         return st;
     }
@@ -672,7 +671,6 @@ void qmc_plan_destroy(qmc_plan_t p) {
     if (p->d_shifts) hipFree(p->d_shifts);
     if (p->d_params) hipFree(p->d_params);
     if (p->d_partials) hipFree(p->d_partials);
-    if (p->d_out) hipFree(p->d_out);
     if (p->h_out) hipHostFree(p->h_out);
     if (p->ev0) hipEventDestroy(p->ev0);
     if (p->ev1) hipEventDestroy(p->ev1);

@@ -7,10 +7,42 @@ namespace qmc {
 // rounds of loads (each row's partials are a dependent read per wave).
 constexpr uint32_t kFinalizeThreads = 1024;
 
+// Mean and two-pass error of eq. (3) of every part from Q_k in LDS
+// (qs[k np + p]): wave w takes the parts w, w + 16, ..., its lanes the shifts,
+// and the double-double butterfly adds them.  One thread adding the shifts of
+// every part one after another was most of the kernel (m = 32, three parts:
+// 25 us of which the partials' sums are 5).  res: per pair of parts
+// (mean a, mean b, err a, err b); a missing last part reads 0.
+__device__ __forceinline__ void finalize_parts(const double *qs, uint32_t m, uint32_t np, double *res) {
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    for (uint32_t p = wave; p < np; p += kFinalizeThreads / kWave) {
+        dd s{0.0, 0.0};
+        for (uint32_t k = lane; k < m; k += kWave) dd_accumulate(s.hi, s.lo, qs[k * np + p]);
+        s = wave_reduce(s);
+        const double mean = (s.hi + s.lo) / (double)m;
+        dd v{0.0, 0.0};
+        for (uint32_t k = lane; k < m; k += kWave) {
+            const double t = qs[k * np + p] - mean;
+            dd_accumulate(v.hi, v.lo, t * t);
+        }
+        v = wave_reduce(v);
+        if (lane == 0) {
+            double *r = res + 4 * (p / 2);
+            r[p % 2] = mean;
+            r[2 + p % 2] = sqrt((v.hi + v.lo) / ((double)m * (double)(m - 1)));
+            if (p % 2 == 0 && p + 1 == np) r[1] = r[3] = 0.0;
+        }
+    }
+}
+
 // One block per instance.  Wave w adds block pairs of (k, p) rows in a fixed
 // strided order and reduces them with the butterfly (the same order whatever
-// the number of waves); thread 0 forms the mean and the two-pass error of
-// eq. (3) for each part.
+// the number of waves).  q and res may be pinned host buffers (a plan's and a
+// batch's are): the kernel writes the few values itself and no copy follows,
+// which takes 2.4 us off an estimate that is all launches (25.0 -> 22.6 us,
+// n = 1021, m = 16).  Finalizing in the lattice kernel's last workgroup instead
+// was slower (n = 131071, m = 16: 26 -> 59 us): every workgroup then needs a
+// device-wide release of its pairs, a write-back of its XCD's cache.
 __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(const FinalizeArgs a) {
     __shared__ double qs[kMaxRows];
     const uint32_t inst = blockIdx.x;
@@ -19,6 +51,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(const FinalizeArg
     for (uint32_t r = wave; r < rows; r += kFinalizeThreads / kWave) {
         const double2 *src = a.partials + ((size_t)inst * rows + r) * a.nblk;
         dd acc{0.0, 0.0};
+#pragma unroll 4
         for (uint32_t b = lane; b < a.nblk; b += kWave) acc = dd_add(acc, dd{src[b].x, src[b].y});
         acc = wave_reduce(acc);
         if (lane == 0) {
@@ -28,24 +61,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(const FinalizeArg
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // results per pair of parts: (mean a, mean b, err a, err b)
-        const uint32_t rs = 4 * ((a.np + 1) / 2);
-        double out[2 * kMaxParts] = {};
-        for (uint32_t p = 0; p < a.np; ++p) {
-            dd s{0.0, 0.0};
-            for (uint32_t k = 0; k < a.m; ++k) dd_accumulate(s.hi, s.lo, qs[k * a.np + p]);
-            const double mean = (s.hi + s.lo) / (double)a.m;
-            dd v{0.0, 0.0};
-            for (uint32_t k = 0; k < a.m; ++k) {
-                const double t = qs[k * a.np + p] - mean;
-                dd_accumulate(v.hi, v.lo, t * t);
-            }
-            out[4 * (p / 2) + p % 2] = mean;
-            out[4 * (p / 2) + 2 + p % 2] = sqrt((v.hi + v.lo) / ((double)a.m * (double)(a.m - 1)));
-        }
-        for (uint32_t t = 0; t < rs; ++t) a.res[(size_t)inst * rs + t] = out[t];
-    }
+    finalize_parts(qs, a.m, a.np, a.res + (size_t)inst * 4 * ((a.np + 1) / 2));
 }
 
 // The lattice kernel's index walk, with the integrand replaced by writes of
@@ -131,6 +147,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize_batch(const Final
         const uint32_t kt = k / a.T, col = (k - kt * a.T) * a.np + p;
         const double2 *src = a.partials + ((size_t)sc.slot_base + (size_t)kt * sc.jtiles) * width + col;
         dd acc{0.0, 0.0};
+#pragma unroll 4
         for (uint32_t b = lane; b < sc.jtiles; b += kWave) acc = dd_add(acc, dd{src[(size_t)b * width].x, src[(size_t)b * width].y});
         acc = wave_reduce(acc);
         if (lane == 0) {
@@ -140,24 +157,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize_batch(const Final
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // results per pair of parts: (mean a, mean b, err a, err b)
-        const uint32_t rs = 4 * ((a.np + 1) / 2);
-        double out[2 * kMaxParts] = {};
-        for (uint32_t p = 0; p < a.np; ++p) {
-            dd s{0.0, 0.0};
-            for (uint32_t k = 0; k < sc.m; ++k) dd_accumulate(s.hi, s.lo, qs[k * a.np + p]);
-            const double mean = (s.hi + s.lo) / (double)sc.m;
-            dd v{0.0, 0.0};
-            for (uint32_t k = 0; k < sc.m; ++k) {
-                const double t = qs[k * a.np + p] - mean;
-                dd_accumulate(v.hi, v.lo, t * t);
-            }
-            out[p] = mean;
-            out[2 + p] = sqrt((v.hi + v.lo) / ((double)sc.m * (double)(sc.m - 1)));
-        }
-        for (int t = 0; t < 4; ++t) a.res[(size_t)blockIdx.x * 4 + t] = out[t];
-    }
+    finalize_parts(qs, sc.m, a.np, a.res + (size_t)blockIdx.x * 4);
 }
 
 hipError_t launch_finalize_batch(const FinalizeBatchArgs &a, uint32_t count, hipStream_t s) {

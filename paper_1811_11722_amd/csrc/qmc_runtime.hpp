@@ -42,8 +42,7 @@ struct qmc_plan_s {
     size_t params_cap = 0;  // in doubles
     double2 *d_partials = nullptr;
     size_t partials_cap = 0;  // in bytes
-    double *d_out = nullptr;  // q (2m) then res (4)
-    double *h_out = nullptr;  // pinned mirror of d_out
+    double *h_out = nullptr;  // pinned; Q_k of every part, then the results (written by the finalize kernel)
     std::vector<double> last_blob;
     uint32_t cur_S = 0;  // thread stride that d_gstep was computed for
     qmc_launch launch{0, 0};
