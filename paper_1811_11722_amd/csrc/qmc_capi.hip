@@ -945,117 +945,4 @@ qmc_status qmc_lattice_dump(qmc_plan_t p, uint64_t j_lo, uint64_t count, uint32_
     return QMC_OK;
 }
 
-qmc_status qmc_korobov_search(uint64_t n, uint32_t d, const uint64_t *cand, uint32_t ncand, uint64_t *a_best,
-                              double *p2_best, double *p2_all) {
-    if (!cand || !a_best || !p2_best) return fail(QMC_EINVAL, "null argument");
-    if (ncand == 0) return fail(QMC_EINVAL, "ncand must be >= 1");
-    if (ncand > 4096) return fail(QMC_EUNSUPPORTED, "ncand > 4096");
-    if (d == 0) return fail(QMC_EINVAL, "d must be >= 1");
-    if (d > kMaxDim) return fail(QMC_EUNSUPPORTED, "d > %u", kMaxDim);
-    if (n < 2) return fail(QMC_EINVAL, "n must be >= 2");
-    if (n > (1ull << 31)) return fail(QMC_EUNSUPPORTED, "n > 2^31");
-    for (uint32_t c = 0; c < ncand; ++c)
-        if (cand[c] % n == 0) return fail(QMC_EINVAL, "candidate %u is 0 mod n", c);
-    const qmc_transform tr{QMC_T_NONE, 0};
-    uint32_t T = 0;
-    LatticeLaunch fn = find_kernel(QMC_F_P2KERNEL, tr, d, 1, T);
-    if (!fn || T != 1) return fail(QMC_EUNSUPPORTED, "no P2 kernel for d = %u", d);
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-    const uint32_t bx = grid_x((uint32_t)n, ncand, dev, 8);
-    std::vector<uint32_t> g((size_t)ncand * d), gs((size_t)ncand * d);
-    for (uint32_t c = 0; c < ncand; ++c) {
-        uint64_t v = 1 % n;
-        for (uint32_t i = 0; i < d; ++i) {
-            g[(size_t)c * d + i] = (uint32_t)v;
-            v = (v * (cand[c] % n)) % n;
-        }
-        gstep_for(&g[(size_t)c * d], d, (uint32_t)n, (uint64_t)bx * kBlock, &gs[(size_t)c * d]);
-    }
-    DeviceScratch s;
-    std::vector<double> zero(d, 0.0), blob(1, 0.0);
-    qmc_status st;
-    if ((st = s.alloc(g.size() * 4)) || (st = s.alloc(gs.size() * 4)) || (st = s.alloc(d * 8)) ||
-        (st = s.alloc(8)) || (st = s.alloc((size_t)ncand * bx * sizeof(double2))) ||
-        (st = s.alloc((size_t)ncand * 8)) || (st = s.alloc((size_t)ncand * 32)))
-        return st;
-    hipStream_t stream = nullptr;
-    if ((e = hipMemcpy(s.ptr[0], g.data(), g.size() * 4, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(s.ptr[1], gs.data(), gs.size() * 4, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(s.ptr[2], zero.data(), d * 8, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(s.ptr[3], blob.data(), 8, hipMemcpyHostToDevice)) != hipSuccess)
-        return hip_fail(e, "search upload");
-    LatticeArgs a{};
-    a.n = (uint32_t)n;
-    a.d = d;
-    a.m = 1;
-    a.tiles = 1;
-    a.inv_n = 1.0 / (double)n;
-    a.g = (const uint32_t *)s.ptr[0];
-    a.gstep = (const uint32_t *)s.ptr[1];
-    a.shifts = (const double *)s.ptr[2];
-    a.params = (const double *)s.ptr[3];
-    a.g_stride = d;
-    a.shift_stride = 0;
-    a.param_stride = 0;
-    a.np = 1;
-    a.partials = (double2 *)s.ptr[4];
-    // The point n - j is the mirror 1 - x of the point j and B2(1 - x) =
-    // B2(x), so the sum S over all points is 2 sum_{j <= n/2} - term(0) -
-    // [n even] term(n/2), term(0) = (1 + pi^2/3)^d.  For even n and odd
-    // candidates every g_i is odd and the point n/2 is (1/2, ..., 1/2) for
-    // all of them; an even candidate puts 0 in some coordinates there, and
-    // then all n points are summed.  Both terms are formed as the kernel
-    // forms them (q(0) is exactly the constant; x = (n/2) / n through 1/n),
-    // multiplied up in order.
-    bool half = true;
-    if ((n & 1) == 0)
-        for (uint32_t c = 0; c < ncand; ++c) half = half && (cand[c] % n) % 2 == 1;
-    double t0 = 0.0;
-    if (half) {
-        const double c2 = 2.0 * 9.869604401089358, c0 = 1.0 + 9.869604401089358 / 3.0;
-        double th = 1.0;
-        if ((n & 1) == 0) {
-            const double x = (double)(n / 2) * (1.0 / (double)n);
-            const double q = std::fma(std::fma(c2, x, -c2), x, c0);
-            th = q;
-            for (uint32_t i = 1; i < d; ++i) th *= q;
-        }
-        t0 = c0;
-        for (uint32_t i = 1; i < d; ++i) t0 *= c0;
-        if ((n & 1) == 0) t0 += th;  // both self-mirrored terms
-    }
-    a.jend = half ? (uint32_t)(n / 2 + 1) : 0;
-    if ((e = fn(a, dim3(bx, ncand), stream)) != hipSuccess) return hip_fail(e, "launch P2 kernel");
-    FinalizeArgs f{};
-    f.partials = a.partials;
-    f.nblk = bx;
-    f.m = 1;
-    f.np = 1;
-    f.n = (double)n;
-    // q = (S - n) / n = ((sum - (n + t0) / 2) 2) / n, t0 the self-mirrored terms
-    f.scale = half ? 2.0 : 1.0;
-    f.sub = half ? ((double)n + t0) / 2.0 : (double)n;
-    f.q = (double *)s.ptr[5];
-    f.res = (double *)s.ptr[6];
-    if ((e = launch_finalize(f, ncand, stream)) != hipSuccess) return hip_fail(e, "launch finalize");
-    std::vector<double> p2(ncand);
-    if ((e = hipMemcpy(p2.data(), s.ptr[5], ncand * 8, hipMemcpyDeviceToHost)) != hipSuccess)
-        return hip_fail(e, "search download");
-    uint64_t best_a = 0;
-    double best = INFINITY;
-    for (uint32_t c = 0; c < ncand; ++c) {
-        if (p2_all) p2_all[c] = p2[c];
-        if (p2[c] < best || (p2[c] == best && cand[c] < best_a)) {
-            best = p2[c];
-            best_a = cand[c];
-        }
-    }
-    if (!std::isfinite(best)) return fail(QMC_ENONFINITE, "P2 not finite");
-    *a_best = best_a;
-    *p2_best = best;
-    return QMC_OK;
-}
-
 }  // extern "C"

@@ -613,3 +613,25 @@ def test_sidi_transform_sectors(Q, m_, cplx):
     _say(f"sector sidi{m_} complex={cplx}")
     res, q, est = _both(Q, "sector", d, n, g, sh, "sidi", m_, sector=tab)
     assert np.all(_rel(q, est.q) < TOL), (_rel(q, est.q).max())
+
+
+@pytest.mark.parametrize("n,d,count", [(2, 1, 1), (3, 16, 2), (257, 1, 3), (1021, 16, 7), (4096, 5, 5), (4096, 2, 64),
+                                       (65521, 3, 1)])
+def test_korobov_search_edges(Q, n, d, count):
+    """The search kernel at its edges: one dimension (only the shared first
+    factor), the most, candidate counts that leave a thread's last candidate
+    unused, n below a workgroup, odd and even n with odd and mixed
+    candidates.  A factor carries a few units of 2^-53 on either side and a
+    product of d of them d times that, relative to the summed magnitudes
+    prod (1 + pi^2/3): 8 d 2^-53 (1 + pi^2/3)^d / n for the largest term plus
+    8 d 2^-53 for the mean of the others, which is near 1."""
+    rng = np.random.default_rng(n + d)
+    cand = np.unique(rng.integers(1, n, 4 * count))[:count].astype(np.uint64)
+    if n == 4096 and count == 64:
+        cand = np.unique(cand | np.uint64(1))
+    _say(f"korobov search n={n} d={d} count={len(cand)}")
+    a, best, every = Q.korobov_search(n, d, cand)
+    _, _, ref = O.korobov_search(n, d, cand, threads=THREADS)
+    tol = 8 * d * 2.0 ** -53 * (1.0 + np.maximum(np.abs(ref), (1 + np.pi ** 2 / 3) ** d / n))
+    assert np.all(np.abs(every - ref) <= tol), (np.abs(every - ref) / tol).max()
+    assert best == every.min() and a == min(int(c) for c, p in zip(cand, every) if p == best)
