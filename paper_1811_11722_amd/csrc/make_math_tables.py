@@ -1,5 +1,6 @@
 """Writes the table of the device logarithm and exponential (qlog and qexp
-in qmc_device.hpp): the initialiser of kMathTab.
+in qmc_device.hpp): the initialiser of kMathTab; with --pow that of kPowTab
+(qexp512, qlog512 and qphase).
 
 Entries 2j and 2j + 1, j = 0..255 (qlog): the mantissa interval
 [1/2 + j/512, 1/2 + (j+1)/512) has the midpoint c_j = 1/2 + (j + 1/2)/512;
@@ -12,6 +13,11 @@ Entry 512 + j, j = 0..511 (qexp): 2^(j/512) rounded to double from 40-digit
 arithmetic; exp(x) = 2^(k >> 9) 2^((k & 511)/512) exp(r) with
 k = rint(512 x / ln 2).
 
+kPowTab holds the exponential's entries again (0 .. 511), then pairs, j =
+0..255: 512 + 2j and 513 + 2j (qlog512) are ic_j and -512 log2(ic_j), 1024 + 2j
+and 1025 + 2j (qphase) the sine and the cosine of 2 pi j / 256, each rounded to
+double from 40-digit arithmetic.
+
 With --poly it writes instead the polynomial coefficients of qatan2 and
 qsincos: Chebyshev interpolants (mpmath.chebyfit, 50 digits; near-minimax)
 of the smooth remainders
@@ -22,7 +28,7 @@ of the smooth remainders
 pi/2 that reduces the sine and cosine argument: two parts of 33 significant
 bits and a remainder rounded to double.
 
-    python make_math_tables.py [--poly]
+    python make_math_tables.py [--pow | --poly]
 """
 import sys
 
@@ -37,11 +43,27 @@ def main():
         ic = 1.0 / (0.5 + (j + 0.5) / 512.0)  # IEEE division: correctly rounded
         lj = float(-mpmath.log(mpmath.mpf(ic)))
         print(f"    {ic.hex()}, {lj.hex()},")
-    print("    // qexp: 2^(j/512), j = 0..511")
+    exp_rows()
+
+
+def exp_rows():
+    print("    // 2^(j/512), j = 0..511")
     for j in range(0, 512, 2):
         a = float(mpmath.power(2, mpmath.mpf(j) / 512))
         b = float(mpmath.power(2, mpmath.mpf(j + 1) / 512))
         print(f"    {a.hex()}, {b.hex()},")
+
+
+def main_pow():
+    exp_rows()
+    print("    // {1/(1/2 + (j + 1/2)/512), -512 log2 of it}, j = 0..255")
+    for j in range(256):
+        ic = 1.0 / (0.5 + (j + 0.5) / 512.0)
+        print(f"    {ic.hex()}, {float(-512 * mpmath.log(mpmath.mpf(ic), 2)).hex()},")
+    print("    // {sin, cos}(2 pi j / 256), j = 0..255")
+    for j in range(256):
+        t = mpmath.mpf(j) / 128  # in units of pi
+        print(f"    {float(mpmath.sinpi(t)).hex()}, {float(mpmath.cospi(t)).hex()},")
 
 
 def _remainder(f, at0):
@@ -95,4 +117,4 @@ def main_poly():
 
 
 if __name__ == "__main__":
-    main_poly() if "--poly" in sys.argv[1:] else main()
+    (main_poly if "--poly" in sys.argv[1:] else main_pow if "--pow" in sys.argv[1:] else main)()

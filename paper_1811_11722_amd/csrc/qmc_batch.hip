@@ -437,16 +437,15 @@ void plan_release_extra(qmc_plan_s *p) {
 // One launch per plan of its run-time specialised sector kernel (each plan's
 // own stream and buffers), then one synchronisation per plan's stream.
 // Launch shape of one plan's specialised sector kernel, as plan_enqueue
-// chooses it (the plan's own configuration, else T = 4 for real sectors of
-// d <= 8, 1 with a deformation, 2 otherwise, and 16 workgroups per CU).
+// chooses it (the plan's own configuration, else jit_tile's shifts per thread
+// and 16 workgroups per CU).
 struct SpecPlan {
     hipFunction_t fn = nullptr;
     uint32_t T = 0, bx = 0, tiles = 0;
 };
 
 static qmc_status spec_prepare(qmc_plan_s *p, const Packed &pk, SpecPlan &sp) {
-    const bool wide = !pk.cplx && p->d <= (pk.orders < 2 ? 8u : 6u);
-    sp.T = p->launch.shift_tile ? p->launch.shift_tile : (pk.deform ? 1u : wide ? 4u : 2u);
+    sp.T = p->launch.shift_tile ? p->launch.shift_tile : jit_tile(pk, p->d);
     std::string err;
     sp.fn = jit_kernel(pk.blob, p->d, p->tr, sp.T, pk.cplx, p->device, err);
     if (!sp.fn) return fail(QMC_EUNSUPPORTED, "specialised sector kernel: %s", err.c_str());

@@ -210,6 +210,9 @@ qmc_status pack_params(int family, uint32_t d, const void *params, Packed &pk) {
             flags |= kSectorComplex | kSectorDeform;
             pk.blob[2] = bits(flags);
             pk.blob.push_back(p->deform_lambda);
+            std::vector<uint64_t> stored;
+            for (uint32_t t : of) stored.push_back(cf[t]);
+            for (const auto &e : derivative_sources(stored, d)) pk.blob.push_back(e.second * p->coef_f[of[e.first]]);
             pk.deform = true;
             pk.cplx = true;
             pk.key_family = kFamSectorComplex;
@@ -343,20 +346,18 @@ uint32_t default_tile(int key_family) {
 }
 
 // Workgroups along the points: about blocks_per_cu (default 8) per CU over
-// all shift tiles, and at most one per kBlock x kMinPointsPerThread points
-// once every CU has one.  Below that floor a thread would walk one or two
-// points and the launch would be all block reductions and partials (one
-// instance of n = 131071, m = 16: 17.4 us -> 13.2 us per kernel with the
-// floor); with fewer workgroups than CUs the walk's length is what the launch
-// waits for, down to one point per thread (n = 16381, m = 16, d = 6 sector: 11.1
-// -> 7.0 us per kernel).
-constexpr uint64_t kMinPointsPerThread = 4;
-
+// all shift tiles, and fewer at small n, where a thread's start (exact products
+// of 64 bits) and the block reduction weigh as much as its walk: at least 32
+// points per thread, down to 4 while there are fewer than two workgroups per CU
+// and to one while some CU has none.  d = 6 sector, m = 32, kernel time: n = 2^20 - 3
+// 150 us with 32 points per thread, 163 with 8; n = 131071 26.6 us with 8 (two
+// workgroups per CU), 29.3 with 4, 28.5 with 16; n = 16381, m = 16 7.0 us with
+// one, 11.1 with four.
 uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu) {
     const uint64_t cus = (uint64_t)device_cu_count(dev), tiles = std::max<uint32_t>(1, tiles_total);
-    const uint64_t bx = std::max<uint64_t>(1, cus * (blocks_per_cu ? blocks_per_cu : 8) / tiles);
     auto groups = [n](uint64_t per) { return (n + kBlock * per - 1) / (kBlock * per); };
-    const uint64_t cap = std::max(groups(kMinPointsPerThread), std::min(groups(1), cus / tiles));
+    const uint64_t cap = std::max({groups(32), std::min(groups(4), 2 * cus / tiles), std::min(groups(1), cus / tiles)});
+    const uint64_t bx = std::max<uint64_t>(1, cus * (blocks_per_cu ? blocks_per_cu : 8) / tiles);
     return (uint32_t)std::max<uint64_t>(std::min(bx, cap), 1);
 }
 
@@ -369,8 +370,9 @@ void gstep_for(const uint32_t *g, uint32_t d, uint32_t n, uint64_t S, uint32_t *
 // past m repeat the last shift (their sums are never read)
 uint32_t padded_rows(uint32_t m) { return (m + kMaxTile - 1) / kMaxTile * kMaxTile; }
 
-// The baker's transform reads its points moved by 1/2 (TrBaker): the device
-// table holds {Delta + 1/2} for it, so the move costs nothing per point.
+// The baker's transform reads its points moved by 1/2 and unwrapped
+// (TrBaker): the device table holds {Delta + 1/2} - 1 for it, so
+// the move costs nothing per point.
 std::vector<double> padded_shifts(const std::vector<double> &sh, uint32_t m, uint32_t d, uint32_t rows,
                                   const qmc_transform &tr) {
     const bool half = tr.kind == QMC_T_BAKER;
@@ -378,7 +380,7 @@ std::vector<double> padded_shifts(const std::vector<double> &sh, uint32_t m, uin
     for (uint32_t r = 0; r < rows; ++r)
         for (uint32_t i = 0; i < d; ++i) {
             const double v = sh[(size_t)std::min(r, m - 1) * d + i];
-            out[(size_t)r * d + i] = !half ? v : (v < 0.5 ? v + 0.5 : v - 0.5);
+            out[(size_t)r * d + i] = !half ? v : (v < 0.5 ? v - 0.5 : v - 1.5);
         }
     return out;
 }
@@ -481,21 +483,25 @@ qmc_status plan_enqueue_fn(qmc_plan_s *p, const Packed &pk, hipFunction_t jfn, u
     return plan_launch(p, pk, nullptr, jfn, T, p->launch.blocks_per_cu);
 }
 
+// Shifts per thread of the specialised kernels: four for real sectors of up to
+// eight dimensions (n = 2^22 - 3, m = 32, four against two: 620, 654, 675 us against
+// 650, 690, 721 under the baker's transform at d = 6, 7, 8, 800, 828, 945 against
+// 850, 897, 974 under Korobov 2; at d = 9 the latter takes 1119 against 1033) and
+// for real expansion orders up to six (8 % slower at d = 8), two for the others
+// (complex d = 10: 707 against 716 us with four), one with a deformation, whose
+// point carries the Jacobian's triangle.
+uint32_t jit_tile(const Packed &pk, uint32_t d) {
+    if (pk.deform) return 1;
+    return !pk.cplx && d <= (pk.orders < 2 ? 8u : 6u) ? 4 : 2;
+}
+
 qmc_status plan_enqueue(qmc_plan_s *p, const Packed &pk, uint32_t want_T, uint32_t bpc) {
     uint32_t T = 0;
     LatticeLaunch fn = nullptr;
     hipFunction_t jfn = nullptr;
     const bool sector = pk.key_family == QMC_F_SECTOR || pk.key_family == kFamSectorComplex;
     if (sector && p->jit_mode != 0) {
-        // four shifts per thread for real sectors of up to eight dimensions
-        // (measured at n = 2^24 - 3, m = 32: 2.19, 2.43, 2.36 ms against
-        // 2.29, 2.50, 2.44 ms with two at d = 6, 7, 8; at d = 9 four run
-        // 27 % slower) and for real expansion orders up to six (three
-        // orders: 2.45 against 2.60 ms at d = 6, 8 % slower at d = 8), two
-        // for the others; a deformed point carries the Jacobian's triangle,
-        // so one
-        const bool wide = !pk.cplx && p->d <= (pk.orders < 2 ? 8u : 6u);
-        T = want_T ? want_T : (pk.deform ? 1u : wide ? 4u : 2u);
+        T = want_T ? want_T : jit_tile(pk, p->d);
         std::string err;
         jfn = jit_kernel(pk.blob, p->d, p->tr, T, pk.cplx, p->device, err);
         if (!jfn && (p->jit_mode == 2 || pk.orders >= 2 || pk.deform))

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kBlock) void k_cv_sample(const CvSampleArgs a) {
 #pragma unroll
     for (int i = 0; i < D; ++i) {
         const uint32_t idx = mulmod(j, a.g[i], a.n, a.inv_n);
-        x[0][i] = fract((double)idx * a.inv_n + a.shift[i]);
+        x[0][i] = Tr::point((double)idx, a.inv_n, a.shift[i]);
     }
     double v[1][Fam::NP], z[1][D], jac[1];
     Fam::template eval<Tr, D, 1>(a.params, x, v);

@@ -12,18 +12,23 @@
 namespace qmc {
 
 // ------------------------------------------------------------ transforms
+// point(i, inv_n, delta) is the coordinate the map takes, from the index i, 1/n
+// and the entry delta of the shift table: the sum i / n + delta is one FMA.
 // Identity: z = x.
 struct TrNone {
     static constexpr bool kJac = false;
+    __device__ static double point(double i, double inv_n, double delta) { return fract(fma_(i, inv_n, delta)); }
     __device__ static double z(double x) { return x; }
     __device__ static double z_operand(double x) { return x; }
 };
 
 // Baker's transform, eq. (5): z = 1 - |2x - 1|.  The map is 2-to-1 with
-// |z'| = 2 on each half, so the integrand weight is 1.  The kernels receive
-// x' = {x + 1/2} (the shift tables of baker plans hold {Delta + 1/2}), and
-// 1 - |2x - 1| = |2x' - 1|.  z() materialises it (one FMA and a v_max with
-// an absolute-value operand, as many instructions as 1 - |2x - 1|);
+// |z'| = 2 on each half, so the integrand weight is 1.  With x' = {x + 1/2},
+// z = |2x' - 1|, a triangle wave; the shift tables of baker plans hold
+// {Delta + 1/2} - 1, so that w = i / n + delta lies in [-1, 1), x' = w or w + 1,
+// and z = |2|w| - 1| on both halves: two FMAs, the second with an absolute-value
+// operand, without the v_fract that the wrapped point would take.
+// z() materialises z (a v_max with an absolute-value operand more);
 // z_operand() is the FMA alone, the absolute value left as a free modifier
 // of each use.  That form suits functors whose uses of z are all FMAs and
 // multiplies (the run-time specialised ones: one instruction less per
@@ -32,8 +37,11 @@ struct TrNone {
 // shifts, a third of the occupancy lost).
 struct TrBaker {
     static constexpr bool kJac = false;
-    __device__ static double z(double xh) { return __builtin_fmax(__builtin_fabs(fma_(2.0, xh, -1.0)), 0.0); }
-    __device__ static double z_operand(double xh) { return __builtin_fabs(fma_(2.0, xh, -1.0)); }
+    __device__ static double point(double i, double inv_n, double delta) { return fma_(i, inv_n, delta); }
+    __device__ static double z(double w) {
+        return __builtin_fmax(__builtin_fabs(fma_(2.0, __builtin_fabs(w), -1.0)), 0.0);
+    }
+    __device__ static double z_operand(double w) { return __builtin_fabs(fma_(2.0, __builtin_fabs(w), -1.0)); }
 };
 
 constexpr double cfact(int k) { return k <= 1 ? 1.0 : k * cfact(k - 1); }
@@ -57,6 +65,7 @@ template <int A>
 struct TrKorobov {
     static_assert(A >= 1 && A <= 6, "Korobov weight 1..6");
     static constexpr bool kJac = true;
+    __device__ static double point(double i, double inv_n, double delta) { return fract(fma_(i, inv_n, delta)); }
     static constexpr double kC = cfact(2 * A + 1) / (cfact(A) * cfact(A));
     // binom(2k, k) as a table evaluated by the compiler: calling the
     // recursive helpers from device code would leave them as run-time calls
@@ -123,6 +132,7 @@ template <int M>
 struct TrSidi {
     static_assert(M >= 1 && M <= 6, "Sidi order 1..6");
     static constexpr bool kJac = true;
+    __device__ static double point(double i, double inv_n, double delta) { return fract(fma_(i, inv_n, delta)); }
     static constexpr int P = M / 2;
     static constexpr double kPiD = 3.141592653589793;
     struct Coefs {
@@ -614,18 +624,18 @@ __device__ __forceinline__ void sector_finish(double mono, double U, double F, u
         const double r = recip(U);
         pre = pre * (r * r);
     } else {
-        lu = pow_u * qlog(U);
+        lu = pow_u * qlog512(U);
     }
     if constexpr (!Complex) {
-        v[0] = pre * qexp(fma_(pow_f, qlog(F), lu));
+        v[0] = pre * qexp512(fma_(pow_f, qlog512(F), lu));
     } else {
         // log(F - i delta) = ln|F - i delta| + i atan2(-delta, F)
         const double mod2 = fma_(F, F, delta * delta);
-        const double e = fma_(0.5 * pow_f, qlog(mod2), lu);
+        const double e = fma_(0.5 * pow_f, qlog512(mod2), lu);
         const double ph = pow_f * qatan2(-delta, F);
         double s, c;
-        qsincos(ph, s, c);
-        const double mag = pre * qexp(e);
+        qphase(ph, s, c);
+        const double mag = pre * qexp512(e);
         v[0] = mag * c;
         v[1] = mag * s;
     }
@@ -640,18 +650,18 @@ template <bool Complex, int NO>
 __device__ __forceinline__ void sector_orders(double mono, double U, double F, uint32_t flags, double pow_u,
                                               double pow_f, double delta, double eps_u, double eps_f,
                                               double (&v)[(Complex ? 2 : 1) * NO]) {
-    const double lnu = qlog(U);
-    double pre = mono;
+    const double lnu = qlog512(U);  // logarithms in units of ln2 / 512
+    double pre = mono, lu = 0.0;
     if (flags & kSectorPowUm2) {
         const double r = recip(U);
         pre = pre * (r * r);
     } else {
-        pre = pre * qexp(pow_u * lnu);
+        lu = pow_u * lnu;
     }
     if constexpr (!Complex) {
-        const double lnf = qlog(F);
-        double f = pre * qexp(pow_f * lnf);
-        const double L = fma_(eps_u, lnu, eps_f * lnf);
+        const double lnf = qlog512(F);
+        double f = pre * qexp512(fma_(pow_f, lnf, lu));
+        const double L = kLnOf512 * fma_(eps_u, lnu, eps_f * lnf);
         v[0] = f;
 #pragma unroll
         for (int k = 1; k < NO; ++k) {
@@ -659,13 +669,13 @@ __device__ __forceinline__ void sector_orders(double mono, double U, double F, u
             v[k] = f;
         }
     } else {
-        const double lnm = 0.5 * qlog(fma_(F, F, delta * delta));  // ln|F - i delta|
-        const double th = qatan2(-delta, F);                        // arg(F - i delta)
+        const double lnm = 0.5 * qlog512(fma_(F, F, delta * delta));  // ln|F - i delta|
+        const double th = qatan2(-delta, F);                           // arg(F - i delta)
         double s, c;
-        qsincos(pow_f * th, s, c);
-        const double mag = pre * qexp(pow_f * lnm);
+        qphase(pow_f * th, s, c);
+        const double mag = pre * qexp512(fma_(pow_f, lnm, lu));
         double fr = mag * c, fi = mag * s;
-        const double lr = fma_(eps_u, lnu, eps_f * lnm), li = eps_f * th;
+        const double lr = kLnOf512 * fma_(eps_u, lnu, eps_f * lnm), li = eps_f * th;
         v[0] = fr;
         v[1] = fi;
 #pragma unroll
@@ -690,44 +700,69 @@ enum : uint32_t { kSectorDeform = 8u };
 enum : uint32_t { kSectorDeformCheck = 16u };
 
 // det(dz/dx) = det(I + i B), B_kl = -lam [s_k H_kl + delta_kl (1 - 2 x_k) g_k],
-// s_k = x_k (1 - x_k), g = grad F, H = Hessian of F.  With r_k = sqrt(s_k),
-// B is similar to the symmetric Bs_kl = -lam [r_k r_l H_kl + delta_kl (1 - 2 x_k) g_k]
-// (a diagonal similarity, so every leading block keeps its determinant;
-// r_k = 0 follows by continuity; each term of det holds r_k r_k, so a
-// rounded s_k slightly below 0 may use r_k = sqrt(|s_k|)).  I + i Bs is complex symmetric with
-// Hermitian part I: each leading block is nonsingular, so the LDL^T
-// factorisation without pivoting exists and det = prod of the pivots.
-// a holds the lower triangle of I + i Bs, row-major packed: (i, j), j <= i, at
-// i (i + 1) / 2 + j; it is overwritten.
+// s_k = x_k (1 - x_k), g = grad F, H = Hessian of F (packed lower triangle, (i, j)
+// at i (i + 1) / 2 + j).  The off-diagonal part is S N with S = diag(s) and N
+// symmetric, and elimination keeps that form:
+//   N_ij -= (s_k / a_k) N_ik N_jk,   a_i -= s_i (s_k / a_k) N_ik^2,
+// so one triangle is held and no square root of s is needed to symmetrise.
+// A diagonal similarity (by sqrt s) makes I + i B symmetric with Hermitian part
+// I without changing the pivots a_k, so Re a_k >= 1, no pivoting is needed and
+// det = prod a_k; s_k = 0 or a rounded s_k slightly below 0 pose no problem.
+// N starts purely imaginary (i m) and a at 1 + i beta, so the first step takes
+// two instructions per entry instead of four.
 template <int D>
-__device__ __forceinline__ void csym_det(double (&ar)[D * (D + 1) / 2], double (&ai)[D * (D + 1) / 2],
-                                         double &dr, double &di) {
-    double pr = 1.0, pi = 0.0;
+__device__ __forceinline__ void deform_det(const double (&x)[D], const double (&s)[D], const double (&g)[D],
+                                           const double (&h)[D * (D + 1) / 2], double lam, double &dr, double &di) {
+    auto at = [](int i, int j) { return i * (i + 1) / 2 + j; };
+    double beta[D];
 #pragma unroll
-    for (int k = 0; k < D; ++k) {
-        const int kk = k * (k + 1) / 2 + k;
-        const double a = ar[kk], b = ai[kk];
+    for (int i = 0; i < D; ++i) beta[i] = -lam * fma_(s[i], h[at(i, i)], fma_(-2.0, x[i], 1.0) * g[i]);
+    dr = 1.0;
+    di = beta[0];
+    if constexpr (D > 1) {
+        double ar[D], ai[D], nr[D * (D + 1) / 2], ni[D * (D + 1) / 2];
         {
-            const double nr = fma_(pr, a, -pi * b), ni = fma_(pr, b, pi * a);
-            pr = nr;
-            pi = ni;
+            // c = s_0 / (1 + i beta_0)
+            const double cr = s[0] * recip(fma_(beta[0], beta[0], 1.0)), ci = -cr * beta[0];
+            double m[D], w[D], u[D];
+#pragma unroll
+            for (int i = 1; i < D; ++i) {
+                m[i] = -lam * h[at(i, 0)];
+                w[i] = m[i] * cr;
+                u[i] = m[i] * ci;
+                const double q = s[i] * m[i];
+                ar[i] = fma_(q, w[i], 1.0);
+                ai[i] = fma_(q, u[i], beta[i]);
+#pragma unroll
+                for (int j = 1; j < i; ++j) {
+                    nr[at(i, j)] = m[i] * w[j];
+                    ni[at(i, j)] = fma_(m[i], u[j], -lam * h[at(i, j)]);
+                }
+            }
         }
-        const double h = recip(fma_(a, a, b * b));
-        const double vr = a * h, vi = -b * h;  // 1 / pivot
 #pragma unroll
-        for (int i = k + 1; i < D; ++i) {
-            const int ik = i * (i + 1) / 2 + k;
-            const double lr = fma_(ar[ik], vr, -ai[ik] * vi), li = fma_(ar[ik], vi, ai[ik] * vr);
+        for (int k = 1; k < D; ++k) {
+            const double pr = fma_(dr, ar[k], -di * ai[k]);
+            di = fma_(dr, ai[k], di * ar[k]);
+            dr = pr;
+            if (k + 1 == D) break;
+            const double hs = s[k] * recip(fma_(ar[k], ar[k], ai[k] * ai[k]));
+            const double cr = ar[k] * hs, ci = -ai[k] * hs;  // s_k / a_k
 #pragma unroll
-            for (int j = k + 1; j <= i; ++j) {
-                const int ij = i * (i + 1) / 2 + j, jk = j * (j + 1) / 2 + k;
-                ar[ij] = ar[ij] - fma_(lr, ar[jk], -li * ai[jk]);
-                ai[ij] = ai[ij] - fma_(lr, ai[jk], li * ar[jk]);
+            for (int i = k + 1; i < D; ++i) {
+                const double br = nr[at(i, k)], bi = ni[at(i, k)];
+                const double lr = fma_(br, cr, -bi * ci), li = fma_(br, ci, bi * cr);
+#pragma unroll
+                for (int j = k + 1; j < i; ++j) {
+                    const double er = nr[at(j, k)], ei = ni[at(j, k)];
+                    nr[at(i, j)] = fma_(li, ei, fma_(-lr, er, nr[at(i, j)]));
+                    ni[at(i, j)] = fma_(-li, er, fma_(-lr, ei, ni[at(i, j)]));
+                }
+                ar[i] = fma_(-s[i], fma_(lr, br, -li * bi), ar[i]);
+                ai[i] = fma_(-s[i], fma_(lr, bi, li * br), ai[i]);
             }
         }
     }
-    dr = pr;
-    di = pi;
 }
 
 // Value (and expansion orders) of the deformed sector integrand:
@@ -741,11 +776,12 @@ __device__ __forceinline__ void sector_deformed(double mr, double mi, double dr,
     fi = fi - delta;
     // pre = mono * det
     double pr = fma_(mr, dr, -mi * di), pim = fma_(mr, di, mi * dr);
-    const double lmf = 0.5 * qlog(fma_(fr, fr, fi * fi)), thf = qatan2(fi, fr);  // ln(F - i delta)
+    // ln(F - i delta), its real part in units of ln2 / 512
+    const double lmf = 0.5 * qlog512(fma_(fr, fr, fi * fi)), thf = qatan2(fi, fr);
     double lmu = 0.0, thu = 0.0;
     double lm = pow_f * lmf, th = pow_f * thf;
     if ((flags & kSectorPowUm2) == 0 || NO >= 2) {
-        lmu = 0.5 * qlog(fma_(ur, ur, ui * ui));
+        lmu = 0.5 * qlog512(fma_(ur, ur, ui * ui));
         thu = qatan2(ui, ur);
     }
     if (flags & kSectorPowUm2) {
@@ -761,13 +797,13 @@ __device__ __forceinline__ void sector_deformed(double mr, double mi, double dr,
         th = fma_(pow_u, thu, th);
     }
     double s, c;
-    qsincos(th, s, c);
-    const double mag = qexp(lm);
+    qphase(th, s, c);
+    const double mag = qexp512(lm);
     double wr = mag * fma_(pr, c, -pim * s), wi = mag * fma_(pr, s, pim * c);
     v[0] = wr;
     v[1] = wi;
     if constexpr (NO >= 2) {
-        const double lr = fma_(eps_u, lmu, eps_f * lmf), li = fma_(eps_u, thu, eps_f * thf);
+        const double lr = kLnOf512 * fma_(eps_u, lmu, eps_f * lmf), li = fma_(eps_u, thu, eps_f * thf);
 #pragma unroll
         for (int k = 1; k < NO; ++k) {
             const double nr = fma_(wr, lr, -wi * li), ni = fma_(wr, li, wi * lr);

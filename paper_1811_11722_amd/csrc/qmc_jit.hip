@@ -1,13 +1,10 @@
 // Run-time specialisation of the sector integrand (hipRTC).
 //
-// The table-driven sector functor reads each monomial's factor list from
-// wave-uniform memory and dispatches on it with scalar branches; on gfx950
-// that dispatch costs more scalar-unit issue than the FP64 work it selects.
-// For a single large sector the exponent structure is fixed for the whole
-// estimate, so this module writes it out as straight-line FP64 code and
-// compiles it once per structure: the monomials of U, F and z^nu become a
-// shared-prefix product trie (each trie edge one multiply, each monomial one
-// fused multiply-add with its coefficient), followed by the same tail as the
+// The table-driven sector functor tests a mask bit for every possible step of
+// its Horner scheme and pays a scalar branch for each.  For a single large
+// sector the exponent structure is fixed for the whole estimate, so this
+// module writes U and F out as straight-line FP64 code in multivariate Horner
+// form and compiles it once per structure, followed by the same tail as the
 // table-driven functor.  Coefficients and powers are still read from the
 // parameter blob, so one compiled kernel serves every coefficient set with
 // the same exponents.  The kernel body is the same k_lattice template,
@@ -88,160 +85,6 @@ const char *transform_type(const qmc_transform &t) {
 
 }  // namespace
 
-// Source of FamJit for a deformed contour (flag 8): straight-line code for
-// the gradient and Hessian of F at the real point (their monomials share a
-// real product trie), the deformed point z - i lam s grad F, the complex
-// monomials of U, F and z^nu at that point (a complex product trie), the
-// symmetrised Jacobian and its determinant, then sector_deformed; a last
-// part counts the points where Im(F(z) - i delta) > 0.
-static std::string deformed_source(uint32_t d, uint32_t flags, uint32_t orders,
-                                   size_t eps_at, size_t lam_at, const std::vector<std::vector<int>> &fu,
-                                   const std::vector<std::vector<int>> &ff, const std::vector<int> &nuf) {
-    Trie rt, ct;  // real (derivative) and complex (deformed point) monomials
-    const uint32_t nu = (uint32_t)fu.size(), nf = (uint32_t)ff.size();
-    struct Term {
-        int coef;   // index into cf
-        int mult;   // integer factor from differentiation
-        int mono;   // real trie node (-1: constant)
-    };
-    std::vector<std::vector<Term>> grad(d);
-    std::vector<std::vector<Term>> hess(d * d);  // (i, j), j <= i, at i * d + j
-    auto drop = [](std::vector<int> f, int v, int &mult) {
-        int cnt = 0;
-        for (int x : f) cnt += x == v;
-        mult *= cnt;
-        if (cnt) f.erase(std::find(f.begin(), f.end(), v));
-        return f;
-    };
-    for (uint32_t t = 0; t < nf; ++t)
-        for (uint32_t i = 0; i < d; ++i) {
-            int mi = 1;
-            const std::vector<int> gi = drop(ff[t], (int)i, mi);
-            if (!mi) continue;
-            grad[i].push_back({(int)t, mi, rt.insert(gi)});
-            for (uint32_t j = 0; j <= i; ++j) {
-                int mj = mi;
-                const std::vector<int> hij = drop(gi, (int)j, mj);
-                if (mj) hess[i * d + j].push_back({(int)t, mj, rt.insert(hij)});
-            }
-        }
-    std::vector<int> cu(nu), cfm(nf);
-    for (uint32_t t = 0; t < nu; ++t) cu[t] = ct.insert(fu[t]);
-    for (uint32_t t = 0; t < nf; ++t) cfm[t] = ct.insert(ff[t]);
-    const int cnu = ct.insert(nuf);
-
-    const uint32_t no = orders >= 2 ? orders : 1u;
-    const bool check = (flags & kSectorDeformCheck) != 0;
-    std::ostringstream s;
-    s << "struct FamJit {\n"
-      << "    static constexpr int NP = " << (check ? 1u : 2 * no + 1) << ";\n"
-      << "    template <class Tr, int D, int T>\n"
-      << "    __device__ static void eval(const double *__restrict__ p, const double (&x)[T][D],"
-         " double (&v)[T][NP]) {\n"
-      << "        double z[T][D], jac[T];\n"
-      << "        apply_transform<Tr, D, T, true>(x, z, jac);\n"
-      << "        constexpr uint32_t flags = " << flags << "u;\n"
-      << "        const __attribute__((address_space(4))) double *cp =\n"
-      << "            (const __attribute__((address_space(4))) double *)p;\n"
-      << "        asm volatile(\"\" : \"+s\"(cp));\n"
-      << "        const double pow_u = cp[3], pow_f = cp[4], delta = cp[5], lam = cp[" << lam_at << "];\n"
-      << "        const double eps_u = " << (orders >= 2 ? "cp[" + std::to_string(eps_at) + "]" : std::string("0.0"))
-      << ", eps_f = " << (orders >= 2 ? "cp[" + std::to_string(eps_at + 1) + "]" : std::string("0.0")) << ";\n"
-      << "        const __attribute__((address_space(4))) double *cu = cp + kSectorHeader;\n"
-      << "        const __attribute__((address_space(4))) double *cf = cu + " << 2 * nu << ";\n"
-      << "#pragma unroll\n"
-      << "        for (int k = 0; k < T; ++k) {\n";
-    // real monomials of the derivatives
-    for (size_t id = 0; id < rt.node.size(); ++id) {
-        const auto &nd = rt.node[id];
-        s << "            const double r" << id << " = ";
-        if (nd.first < 0) s << "z[k][" << nd.second << "];\n";
-        else s << "r" << nd.first << " * z[k][" << nd.second << "];\n";
-    }
-    auto sum = [&](const std::string &name, const std::vector<Term> &terms) {
-        s << "            double " << name << " = 0.0;\n";
-        for (const Term &t : terms) {
-            std::ostringstream c;
-            if (t.mult == 1) c << "cf[" << t.coef << "]";
-            else c << "(cf[" << t.coef << "] * " << t.mult << ".0)";
-            if (t.mono < 0) s << "            " << name << " = " << name << " + " << c.str() << ";\n";
-            else s << "            " << name << " = fma_(" << c.str() << ", r" << t.mono << ", " << name << ");\n";
-        }
-    };
-    for (uint32_t i = 0; i < d; ++i) sum("g" + std::to_string(i), grad[i]);
-    if (!check)
-        for (uint32_t i = 0; i < d; ++i)
-            for (uint32_t j = 0; j <= i; ++j) sum("h" + std::to_string(i) + "_" + std::to_string(j), hess[i * d + j]);
-    // the deformed point: real part z, imaginary part y
-    for (uint32_t i = 0; i < d; ++i)
-        s << "            const double s" << i << " = z[k][" << i << "] * (1.0 - z[k][" << i << "]);\n"
-          << "            const double y" << i << " = -lam * (s" << i << " * g" << i << ");\n";
-    // complex monomials at the deformed point
-    for (size_t id = 0; id < ct.node.size(); ++id) {
-        const auto &nd = ct.node[id];
-        const int v = nd.second;
-        if (nd.first < 0) {
-            s << "            const double c" << id << "r = z[k][" << v << "], c" << id << "i = y" << v << ";\n";
-        } else {
-            const int q = nd.first;
-            s << "            const double c" << id << "r = fma_(c" << q << "r, z[k][" << v << "], -(c" << q << "i * y" << v
-              << ")), c" << id << "i = fma_(c" << q << "r, y" << v << ", c" << q << "i * z[k][" << v << "]);\n";
-        }
-    }
-    auto cpoly = [&](const char *name, const char *coef, const std::vector<int> &mono) {
-        s << "            double " << name << "r = 0.0, " << name << "i = 0.0;\n";
-        for (size_t t = 0; t < mono.size(); ++t) {
-            if (mono[t] < 0) {
-                s << "            " << name << "r = " << name << "r + " << coef << "[" << t << "];\n";
-            } else {
-                s << "            " << name << "r = fma_(" << coef << "[" << t << "], c" << mono[t] << "r, " << name
-                  << "r);\n";
-                s << "            " << name << "i = fma_(" << coef << "[" << t << "], c" << mono[t] << "i, " << name
-                  << "i);\n";
-            }
-        }
-    };
-    if (check) {
-        cpoly("F", "cf", cfm);
-        s << "            v[k][0] = Fi - delta > 0.0 ? 1.0 : 0.0;\n"
-          << "        }\n    }\n};\n";
-        return s.str();
-    }
-    cpoly("U", "cu", cu);
-    cpoly("F", "cf", cfm);
-    if (cnu < 0) s << "            const double mr = jac[k], mi = 0.0;\n";
-    else s << "            const double mr = jac[k] * c" << cnu << "r, mi = jac[k] * c" << cnu << "i;\n";
-    // I + i Bs, packed lower triangle
-    const uint32_t nt = d * (d + 1) / 2;
-    s << "            double ar[" << nt << "], ai[" << nt << "];\n";
-    // a transformed coordinate may round a few ulp outside [0, 1], making s
-    // slightly negative: every term of det pairs q_k with itself (q_k^2
-    // stands for s_k), so |s_k| changes det by O(|s_k|) only
-    for (uint32_t i = 0; i < d; ++i)
-        s << "            const double q" << i << " = __builtin_sqrt(__builtin_fabs(s" << i << "));\n";
-    for (uint32_t i = 0; i < d; ++i)
-        for (uint32_t j = 0; j <= i; ++j) {
-            const uint32_t ij = i * (i + 1) / 2 + j;
-            s << "            ar[" << ij << "] = " << (i == j ? "1.0" : "0.0") << ";\n";
-            s << "            ai[" << ij << "] = -lam * ";
-            if (i == j)
-                s << "fma_(s" << i << ", h" << i << "_" << i << ", (1.0 - 2.0 * z[k][" << i << "]) * g" << i << ");\n";
-            else
-                s << "((q" << i << " * q" << j << ") * h" << i << "_" << j << ");\n";
-        }
-    // the value parts, then 1 where the contour is on the wrong side (the
-    // sign check of the deformation, counted in the same pass)
-    s << "            double dr, di, w[" << 2 * no << "];\n"
-      << "            csym_det<D>(ar, ai, dr, di);\n"
-      << "            sector_deformed<" << no
-      << ">(mr, mi, dr, di, Ur, Ui, Fr, Fi, flags, pow_u, pow_f, delta, eps_u, eps_f, w);\n"
-      << "#pragma unroll\n"
-      << "            for (int j = 0; j < " << 2 * no << "; ++j) v[k][j] = w[j];\n"
-      << "            v[k][" << 2 * no << "] = Fi - delta > 0.0 ? 1.0 : 0.0;\n"
-      << "        }\n    }\n};\n";
-    return s.str();
-}
-
 // Multivariate Horner form of sum_t coef[t] prod_i z_i^e[t][i]: split off
 // the variable v that occurs in most non-constant terms, P = P0 + z_v P1,
 // and recurse on P1 (exponents of v lowered) and P0.  Each split costs one
@@ -250,15 +93,8 @@ static std::string deformed_source(uint32_t d, uint32_t flags, uint32_t orders,
 // FMA per term.  Emits the temporaries (arrays over the thread's shifts k)
 // into s and returns the expression of the value for shift k.
 using HornerTerms = std::vector<std::pair<int, std::vector<int>>>;
-static std::string horner(const char *coef, HornerTerms terms, std::ostringstream &s, int &tmp) {
-    HornerTerms consts;
-    for (const auto &t : terms)
-        if (std::all_of(t.second.begin(), t.second.end(), [](int e) { return e == 0; })) consts.push_back(t);
-    if (consts.size() == terms.size()) {
-        std::ostringstream e;
-        for (size_t c = 0; c < consts.size(); ++c) e << (c ? " + " : "") << coef << "[" << consts[c].first << "]";
-        return consts.size() == 1 ? e.str() : "(" + e.str() + ")";
-    }
+// the split P = P0 + z_v P1; returns v
+static size_t horner_split(const HornerTerms &terms, HornerTerms &p1, HornerTerms &p0) {
     const size_t nv = terms[0].second.size();
     size_t v = 0;
     int best = -1;
@@ -270,7 +106,6 @@ static std::string horner(const char *coef, HornerTerms terms, std::ostringstrea
             v = i;
         }
     }
-    HornerTerms p1, p0;
     for (auto t : terms) {
         if (t.second[v] > 0) {
             t.second[v] -= 1;
@@ -279,6 +114,20 @@ static std::string horner(const char *coef, HornerTerms terms, std::ostringstrea
             p0.push_back(t);
         }
     }
+    return v;
+}
+
+static std::string horner(const char *coef, HornerTerms terms, std::ostringstream &s, int &tmp) {
+    HornerTerms consts;
+    for (const auto &t : terms)
+        if (std::all_of(t.second.begin(), t.second.end(), [](int e) { return e == 0; })) consts.push_back(t);
+    if (consts.size() == terms.size()) {
+        std::ostringstream e;
+        for (size_t c = 0; c < consts.size(); ++c) e << (c ? " + " : "") << coef << "[" << consts[c].first << "]";
+        return consts.size() == 1 ? e.str() : "(" + e.str() + ")";
+    }
+    HornerTerms p1, p0;
+    const size_t v = horner_split(terms, p1, p0);
     const std::string a = horner(coef, p1, s, tmp);
     const std::string b = p0.empty() ? std::string() : horner(coef, p0, s, tmp);
     // one statement per line over the T shifts of the thread, so that a
@@ -303,22 +152,23 @@ static std::string launder_chunks(const std::string &text) {
     std::istringstream in(text);
     std::ostringstream out;
     std::string line;
-    int next[2] = {0, 0};  // next chunk start for cu, cf
+    int next[3] = {0, 0, 0};  // next chunk start for cu, cf, dc
     int ptr = 0;
     while (std::getline(in, line)) {
         std::string fixed;
         std::string pre;
         for (size_t i = 0; i < line.size();) {
-            const bool is_u = line.compare(i, 3, "cu[") == 0, is_f = line.compare(i, 3, "cf[") == 0;
-            if ((!is_u && !is_f) || (i > 0 && (std::isalnum((unsigned char)line[i - 1]) || line[i - 1] == '_'))) {
+            const bool is_u = line.compare(i, 3, "cu[") == 0, is_f = line.compare(i, 3, "cf[") == 0,
+                       is_d = line.compare(i, 3, "dc[") == 0;
+            if ((!is_u && !is_f && !is_d) || (i > 0 && (std::isalnum((unsigned char)line[i - 1]) || line[i - 1] == '_'))) {
                 fixed += line[i++];
                 continue;
             }
             size_t j = i + 3;
             int v = 0;
             while (j < line.size() && std::isdigit((unsigned char)line[j])) v = 10 * v + (line[j++] - '0');
-            const int w = is_u ? 0 : 1;
-            const char *base = is_u ? "cu" : "cf";
+            const int w = is_u ? 0 : is_f ? 1 : 2;
+            const char *base = is_u ? "cu" : is_f ? "cf" : "dc";
             if (v >= next[w]) {
                 ++ptr;
                 pre += std::string("            const __attribute__((address_space(4))) double *q") +
@@ -338,54 +188,231 @@ static std::string launder_chunks(const std::string &text) {
 // The host packer stores the terms in this order, so the generated code
 // reads the coefficients in ascending address order and the compiler can
 // fetch them with few scalar loads and few live scalar registers.
-static std::vector<uint32_t> horner_term_order_uncached(const std::vector<uint64_t> &codes, uint32_t d) {
+static HornerTerms terms_of(const std::vector<uint64_t> &codes, uint32_t d) {
     HornerTerms terms;
     for (size_t t = 0; t < codes.size(); ++t) {
         std::vector<int> e(d, 0);
         for (int v : factors_of(codes[t])) e[v] += 1;
         terms.push_back({(int)t, e});
     }
+    return terms;
+}
+
+// indices (the first of each pair, 0 .. terms.size() - 1) in reading order
+static std::vector<uint32_t> reading_order(const HornerTerms &terms) {
     std::ostringstream s;
     int tmp = 0;
-    const std::string top = horner("c", terms, s, tmp);
+    const std::string top = terms.empty() ? std::string() : horner("c", terms, s, tmp);
     s << top;
     const std::string text = s.str();
     std::vector<uint32_t> order;
-    std::vector<bool> seen(codes.size(), false);
+    std::vector<bool> seen(terms.size(), false);
     for (size_t i = 0; i + 1 < text.size(); ++i) {
         if (text[i] != 'c' || text[i + 1] != '[') continue;
         size_t j = i + 2;
         uint32_t v = 0;
         while (j < text.size() && text[j] >= '0' && text[j] <= '9') v = 10 * v + (uint32_t)(text[j++] - '0');
-        if (v < codes.size() && !seen[v]) {
+        if (v < terms.size() && !seen[v]) {
             seen[v] = true;
             order.push_back(v);
         }
     }
-    for (uint32_t t = 0; t < codes.size(); ++t)
+    for (uint32_t t = 0; t < terms.size(); ++t)
         if (!seen[t]) order.push_back(t);
     return order;
 }
 
-// Remembered per (d, codes): a plan re-packs its integrand at every estimate.
-std::vector<uint32_t> horner_term_order(const std::vector<uint64_t> &codes, uint32_t d) {
-    static std::mutex mu;
-    static std::unordered_map<std::string, std::vector<uint32_t>> memo;
-    std::string key(sizeof(uint32_t) + codes.size() * sizeof(uint64_t), '\0');
-    std::memcpy(&key[0], &d, sizeof(uint32_t));
-    if (!codes.empty()) std::memcpy(&key[sizeof(uint32_t)], codes.data(), codes.size() * sizeof(uint64_t));
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        auto it = memo.find(key);
-        if (it != memo.end()) return it->second;
-    }
-    std::vector<uint32_t> order = horner_term_order_uncached(codes, d);
-    std::lock_guard<std::mutex> lock(mu);
-    if (memo.size() >= 65536) memo.clear();  // bounded: structures of one run rarely exceed it
-    memo.emplace(key, order);
-    return order;
+// The gradient (i = 0 .. d - 1) and then the lower triangle of the Hessian
+// ((0,0), (1,0), (1,1), ...) of the polynomial with these monomials: per
+// derivative its terms in the order its Horner code reads them, the index of
+// each counting all of them through (the deformed functor's table), and in
+// `source` for every table entry the polynomial's term and the integer factor
+// from differentiation.
+struct Derivatives {
+    std::vector<HornerTerms> poly;
+    std::vector<std::pair<uint32_t, int>> source;
+};
+static Derivatives derivatives_of(const std::vector<uint64_t> &codes, uint32_t d) {
+    const HornerTerms f = terms_of(codes, d);
+    Derivatives out;
+    auto add = [&](uint32_t i, int j) {  // d/dz_i, then d/dz_j unless j < 0
+        HornerTerms terms;
+        std::vector<std::pair<uint32_t, int>> src;
+        for (const auto &t : f) {
+            std::vector<int> e = t.second;
+            int mult = e[i]--;
+            if (mult && j >= 0) mult *= e[j]--;
+            if (mult <= 0) continue;
+            terms.push_back({(int)terms.size(), e});
+            src.push_back({(uint32_t)t.first, mult});
+        }
+        HornerTerms sorted;
+        for (uint32_t t : reading_order(terms)) {
+            sorted.push_back({(int)out.source.size(), terms[t].second});
+            out.source.push_back(src[t]);
+        }
+        out.poly.push_back(sorted);
+    };
+    for (uint32_t i = 0; i < d; ++i) add(i, -1);
+    for (uint32_t i = 0; i < d; ++i)
+        for (uint32_t j = 0; j <= i; ++j) add(i, (int)j);
+    return out;
 }
 
+// A result remembered per (d, codes); bounded: the structures of one run rarely
+// exceed it
+template <class V>
+struct StructureMemo {
+    std::mutex mu;
+    std::unordered_map<std::string, V> map;
+    template <class Fn>
+    V get(const std::vector<uint64_t> &codes, uint32_t d, Fn &&make) {
+        std::string key(sizeof(uint32_t) + codes.size() * sizeof(uint64_t), '\0');
+        std::memcpy(&key[0], &d, sizeof(uint32_t));
+        if (!codes.empty()) std::memcpy(&key[sizeof(uint32_t)], codes.data(), codes.size() * sizeof(uint64_t));
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            auto it = map.find(key);
+            if (it != map.end()) return it->second;
+        }
+        V v = make();
+        std::lock_guard<std::mutex> lock(mu);
+        if (map.size() >= 65536) map.clear();
+        map.emplace(key, v);
+        return v;
+    }
+};
+
+// Remembered: a plan re-packs its integrand at every estimate.
+std::vector<uint32_t> horner_term_order(const std::vector<uint64_t> &codes, uint32_t d) {
+    static StructureMemo<std::vector<uint32_t>> memo;
+    return memo.get(codes, d, [&] { return reading_order(terms_of(codes, d)); });
+}
+
+std::vector<std::pair<uint32_t, int>> derivative_sources(const std::vector<uint64_t> &codes, uint32_t d) {
+    static StructureMemo<std::vector<std::pair<uint32_t, int>>> memo;
+    return memo.get(codes, d, [&] { return derivatives_of(codes, d).source; });
+}
+
+// The Horner form at the complex point z_v + i y_v (arrays z[k][v], y[k][v]):
+// a split costs four FMAs, two where the multiplied part is a coefficient.
+struct ComplexExpr {
+    std::string re, im;  // im empty: real
+};
+static ComplexExpr complex_horner(const char *coef, const HornerTerms &terms, std::ostringstream &s, int &tmp) {
+    bool constant = true;
+    for (const auto &t : terms)
+        for (int e : t.second) constant = constant && e == 0;
+    if (constant) {
+        std::string e;
+        for (const auto &t : terms) e += (e.empty() ? "" : " + ") + (std::string(coef) + "[" + std::to_string(t.first) + "]");
+        return {terms.size() == 1 ? e : "(" + e + ")", ""};
+    }
+    HornerTerms p1, p0;
+    const std::string v = std::to_string(horner_split(terms, p1, p0));
+    const ComplexExpr a = complex_horner(coef, p1, s, tmp);
+    const ComplexExpr b = p0.empty() ? ComplexExpr{} : complex_horner(coef, p0, s, tmp);
+    const std::string n = std::to_string(tmp++), zr = "z[k][" + v + "]", zi = "y[k][" + v + "]";
+    auto fma = [](const std::string &x, const std::string &w, const std::string &add) {
+        return add.empty() ? x + " * " + w : "fma_(" + x + ", " + w + ", " + add + ")";
+    };
+    std::string re = fma(a.re, zr, b.re), im = fma(a.re, zi, b.im);
+    if (!a.im.empty()) {
+        re = "fma_(-" + a.im + ", " + zi + ", " + re + ")";
+        im = "fma_(" + a.im + ", " + zr + ", " + im + ")";
+    }
+    s << "        double cr" << n << "[T], ci" << n << "[T]; _Pragma(\"unroll\") for (int k = 0; k < T; ++k) { cr" << n
+      << "[k] = " << re << "; ci" << n << "[k] = " << im << "; }\n";
+    return {"cr" + n + "[k]", "ci" + n + "[k]"};
+}
+
+// Source of FamJit for a deformed contour (flag 8): straight-line code for
+// the gradient and Hessian of F at the real point (Horner forms; their
+// coefficients, the polynomial's times the integers from differentiation,
+// come in reading order from a table of their own), the deformed point z +
+// i y, y = -lam s grad F, U and F at it (complex Horner forms), z^nu, the
+// determinant of the Jacobian, then sector_deformed; a last part counts the
+// points where Im(F(z) - i delta) > 0.  Bound by VALU issue.  d = 6, U 12 and F
+// 30 monomials: 852 vector instructions per evaluation against 1148 with one product
+// per monomial, integer factors multiplied per point and a symmetrised Jacobian
+// (a square root per coordinate).
+static std::string deformed_source(uint32_t d, uint32_t flags, uint32_t orders, size_t eps_at, size_t lam_at,
+                                   const std::vector<uint64_t> &cu, const std::vector<uint64_t> &cf,
+                                   const std::vector<int> &nuf) {
+    const uint32_t no = orders >= 2 ? orders : 1u;
+    const bool check = (flags & kSectorDeformCheck) != 0;
+    const Derivatives dv = derivatives_of(cf, d);
+    std::ostringstream s;
+    s << "struct FamJit {\n"
+      << "    static constexpr int NP = " << (check ? 1u : 2 * no + 1) << ";\n"
+      << "    static constexpr bool kShiftsInLds = true;\n"
+      << "    template <class Tr, int D, int T>\n"
+      << "    __device__ static void eval(const double *__restrict__ p, const double (&x)[T][D],"
+         " double (&v)[T][NP]) {\n"
+      << "        double z[T][D], jac[T];\n"
+      << "        apply_transform<Tr, D, T, true>(x, z, jac);\n"
+      << "        constexpr uint32_t flags = " << flags << "u;\n"
+      << "        const __attribute__((address_space(4))) double *cp =\n"
+      << "            (const __attribute__((address_space(4))) double *)p;\n"
+      << "        asm volatile(\"\" : \"+s\"(cp));\n"
+      << "        const double pow_u = cp[3], pow_f = cp[4], delta = cp[5], lam = cp[" << lam_at << "];\n"
+      << "        const double eps_u = " << (orders >= 2 ? "cp[" + std::to_string(eps_at) + "]" : std::string("0.0"))
+      << ", eps_f = " << (orders >= 2 ? "cp[" + std::to_string(eps_at + 1) + "]" : std::string("0.0")) << ";\n"
+      << "        const __attribute__((address_space(4))) double *cu = cp + kSectorHeader;\n"
+      << "        const __attribute__((address_space(4))) double *cf = cu + " << 2 * cu.size() << ";\n"
+      << "        const __attribute__((address_space(4))) double *dc = cp + " << lam_at + 1 << ";\n"
+      << "        double y[T][D], s[T][D], g[T][D];\n";
+    std::ostringstream b;  // the parts that read coefficients
+    int tmp = 0;
+    for (uint32_t i = 0; i < d; ++i) {
+        const std::string e = dv.poly[i].empty() ? std::string("0.0") : horner("dc", dv.poly[i], b, tmp);
+        b << "        _Pragma(\"unroll\") for (int k = 0; k < T; ++k) { g[k][" << i << "] = " << e << "; s[k][" << i
+          << "] = z[k][" << i << "] * (1.0 - z[k][" << i << "]); y[k][" << i << "] = -lam * (s[k][" << i << "] * g[k]["
+          << i << "]); }\n";
+    }
+    if (!check) {
+        b << "        double h[T][" << d * (d + 1) / 2 << "];\n";
+        for (uint32_t q = 0; q < d * (d + 1) / 2; ++q) {
+            const HornerTerms &t = dv.poly[d + q];
+            const std::string e = t.empty() ? std::string("0.0") : horner("dc", t, b, tmp);
+            b << "        _Pragma(\"unroll\") for (int k = 0; k < T; ++k) h[k][" << q << "] = " << e << ";\n";
+        }
+    }
+    auto at_point = [&](const char *name, const char *coef, const std::vector<uint64_t> &codes) {
+        const ComplexExpr e = complex_horner(coef, terms_of(codes, d), b, tmp);
+        b << "        double " << name << "r[T], " << name << "i[T]; _Pragma(\"unroll\") for (int k = 0; k < T; ++k) { "
+          << name << "r[k] = " << e.re << "; " << name << "i[k] = " << (e.im.empty() ? std::string("0.0") : e.im)
+          << "; }\n";
+    };
+    if (!check) at_point("U", "cu", cu);
+    at_point("F", "cf", cf);
+    s << launder_chunks(b.str()) << "#pragma unroll\n        for (int k = 0; k < T; ++k) {\n";
+    if (check) {
+        s << "            v[k][0] = Fi[k] - delta > 0.0 ? 1.0 : 0.0;\n        }\n    }\n};\n";
+        return s.str();
+    }
+    // z^nu times the transform's weight
+    s << "            double mr = jac[k], mi = 0.0;\n";
+    for (size_t q = 0; q < nuf.size(); ++q) {
+        const int i = nuf[q];
+        if (q == 0)
+            s << "            mi = mr * y[k][" << i << "]; mr = mr * z[k][" << i << "];\n";
+        else
+            s << "            { const double t = fma_(mr, y[k][" << i << "], mi * z[k][" << i << "]); mr = fma_(mr, z[k]["
+              << i << "], -(mi * y[k][" << i << "])); mi = t; }\n";
+    }
+    // the value parts, then 1 where the contour is on the wrong side (the
+    // sign check of the deformation, counted in the same pass)
+    s << "            double dr, di, w[" << 2 * no << "];\n"
+      << "            deform_det<D>(z[k], s[k], g[k], h[k], lam, dr, di);\n"
+      << "            sector_deformed<" << no
+      << ">(mr, mi, dr, di, Ur[k], Ui[k], Fr[k], Fi[k], flags, pow_u, pow_f, delta, eps_u, eps_f, w);\n"
+      << "#pragma unroll\n"
+      << "            for (int j = 0; j < " << 2 * no << "; ++j) v[k][j] = w[j];\n"
+      << "            v[k][" << 2 * no << "] = Fi[k] - delta > 0.0 ? 1.0 : 0.0;\n"
+      << "        }\n    }\n};\n";
+    return s.str();
+}
 
 // A canonical description of everything the specialised functor of one
 // sector blob depends on (dimension, complex flag, monomial codes, flags,
@@ -438,17 +465,17 @@ static std::string functor_source(const std::vector<double> &blob, uint32_t d, b
     if (flags & kSectorDeform) {
         // the deformation parameter follows the orders words (if any)
         const size_t lam_at = eps_at + ((flags & kSectorOrders) ? 3u : 0u);
-        std::vector<std::vector<int>> fu(nu), ff(nf);
-        for (uint32_t t = 0; t < nu; ++t) fu[t] = factors_of(word(blob, kSectorHeader + nu + t));
-        for (uint32_t t = 0; t < nf; ++t) ff[t] = factors_of(word(blob, kSectorHeader + 2 * nu + nf + t));
-        return deformed_source(d, flags, orders, eps_at, lam_at, fu, ff, nuf);
+        std::vector<uint64_t> cu(nu), cf(nf);
+        for (uint32_t t = 0; t < nu; ++t) cu[t] = word(blob, kSectorHeader + nu + t);
+        for (uint32_t t = 0; t < nf; ++t) cf[t] = word(blob, kSectorHeader + 2 * nu + nf + t);
+        return deformed_source(d, flags, orders, eps_at, lam_at, cu, cf, nuf);
     }
 
     std::ostringstream s;
     const uint32_t np = (cplx ? 2u : 1u) * (orders >= 2 ? orders : 1u);
     s << "struct FamJit {\n"
       << "    static constexpr int NP = " << np << ";\n"
-      << "    static constexpr bool kShiftsInVgprs = true;\n"
+      << "    static constexpr bool kShiftsInLds = true;\n"
       << "    template <class Tr, int D, int T>\n"
       << "    __device__ static void eval(const double *__restrict__ p, const double (&x)[T][D],"
          " double (&v)[T][NP]) {\n"
@@ -527,7 +554,7 @@ static std::string sum_source(const std::vector<double> &blob, const std::vector
     std::ostringstream s;
     s << "struct FamJit {\n"
       << "    static constexpr int NP = " << np << ";\n"
-      << "    static constexpr bool kShiftsInVgprs = true;\n"
+      << "    static constexpr bool kShiftsInLds = true;\n"
       << "    template <class Tr, int D, int T>\n"
       << "    __device__ static void eval(const double *__restrict__ p, const double (&x)[T][D],"
          " double (&v)[T][NP]) {\n"

@@ -6,8 +6,7 @@
 // j = t, t + S, t + 2S, ...; its indices idx_i = (j g_i) mod n start from
 // one exact 64-bit product and then advance by the precomputed
 // (S g_i) mod n with a single conditional wrap, so the lattice is walked
-// exactly in 32-bit integers.  idx_i / n is shared by the T shifts of the
-// tile.  Sums are compensated: a plain FP64 partial over a chunk of points is
+// exactly in 32-bit integers; the T shifts of the tile share it.  Sums are compensated: a plain FP64 partial over a chunk of points is
 // folded into a (hi, lo) pair with TwoSum, the wave reduces the pairs with a
 // double-double butterfly, LDS joins the 4 waves, and one pair per block
 // and shift goes to HBM.  k_finalize then adds the block pairs in a fixed
@@ -56,19 +55,19 @@ template <class F>
 __device__ constexpr bool wave_uniform_walk(long) {
     return false;
 }
-// A family that sets kShiftsInVgprs = true has the T x D shift values of
-// its tile copied into vector registers before the point loop.  Held as
-// scalars they compete with the integrand's coefficients for the 106 scalar
-// registers, and the compiler spills them into vector lanes, paying a
-// v_readlane per value and point; the run-time specialised sector functors
-// have vector registers to spare and ask for this (for tiles of up to 24
-// values).
+// A family that sets kShiftsInLds = true has the T x D shift values of its
+// tile staged in LDS, and every point reads them from there (broadcast reads,
+// which cost no vector instruction).  Held as scalars they compete with the
+// integrand's coefficients for the 106 scalar registers, and the compiler
+// spills them into vector lanes, paying a v_readlane per value and point; held
+// in vector registers they take 2 T D of them.  The run-time specialised
+// sector functors ask for this.
 template <class F>
-__device__ constexpr auto shifts_in_vgprs(int) -> decltype(F::kShiftsInVgprs, bool()) {
-    return F::kShiftsInVgprs;
+__device__ constexpr auto shifts_in_lds(int) -> decltype(F::kShiftsInLds, bool()) {
+    return F::kShiftsInLds;
 }
 template <class F>
-__device__ constexpr bool shifts_in_vgprs(long) {
+__device__ constexpr bool shifts_in_lds(long) {
     return false;
 }
 
@@ -93,16 +92,8 @@ __device__ __forceinline__ void walk_points(uint32_t j, uint32_t j1, uint32_t S,
         step[i] = gs[i];
         nms[i] = n - gs[i];
     }
-    // (bounded: 24 doubles are 48 VGPRs; larger tiles keep the scalar copies)
-    constexpr bool kVgprShifts = !Reload && shifts_in_vgprs<Fam>(0) && T * D <= 24;
-    double dlv[T * D];
-    if constexpr (kVgprShifts) {
-#pragma unroll
-        for (int q = 0; q < T * D; ++q) {
-            dlv[q] = dls[q];
-            asm volatile("" : "+v"(dlv[q]));  // a vector register from here on
-        }
-    }
+    // scalar shifts leave no scalar operand for 1/n in the point's FMA
+    const double rn = shifts_in_lds<Fam>(0) ? inv_n : vreg_const(inv_n);
 #pragma unroll 1
     while (more()) {
         double s[T][NP];
@@ -115,7 +106,7 @@ __device__ __forceinline__ void walk_points(uint32_t j, uint32_t j1, uint32_t S,
             double y[D];
 #pragma unroll
             for (int i = 0; i < D; ++i) {
-                y[i] = (double)idx[i] * inv_n;
+                y[i] = (double)idx[i];
                 idx[i] = walk(idx[i], step[i], nms[i]);
             }
             const double *dl = dls;
@@ -123,11 +114,13 @@ __device__ __forceinline__ void walk_points(uint32_t j, uint32_t j1, uint32_t S,
                 dl = uniform_ptr(dls);
                 asm volatile("" : "+s"(dl));  // keep the shift loads inside the loop
             }
+            // staged shifts are read anew at every point, not hoisted
+            if constexpr (shifts_in_lds<Fam>(0)) asm volatile("" ::: "memory");
             double x[T][D];
 #pragma unroll
             for (int k = 0; k < T; ++k)
 #pragma unroll
-                for (int i = 0; i < D; ++i) x[k][i] = fract(y[i] + (kVgprShifts ? dlv[k * D + i] : dl[k * D + i]));
+                for (int i = 0; i < D; ++i) x[k][i] = Tr::point(y[i], rn, dl[k * D + i]);
             double v[T][NP];
             Fam::template eval<Tr, D, T>(prm, x, v);
             const bool ok = !kUniform || j < j1;
@@ -150,13 +143,23 @@ template <int T, int NP>
 __device__ __forceinline__ dd block_reduce(const double (&hi)[T][NP], const double (&lo)[T][NP],
                                            dd (&red)[kBlock / kWave][T * NP]) {
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    constexpr int R = pow2_at_least(T * NP);
+    if constexpr (R <= kWave) {
+        dd v[R];
 #pragma unroll
-    for (int k = 0; k < T; ++k)
+        for (int r = 0; r < R; ++r) v[r] = r < T * NP ? dd{hi[r / NP][r % NP], lo[r / NP][r % NP]} : dd{0.0, 0.0};
+        const dd t = wave_reduce_rows<R>(v);
+        constexpr uint32_t step = kWave / R;
+        if (lane % step == 0 && lane / step < (uint32_t)(T * NP)) red[wave][lane / step] = t;
+    } else {
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            dd r = wave_reduce(dd{hi[k][p], lo[k][p]});
-            if (lane == 0) red[wave][k * NP + p] = r;
-        }
+        for (int k = 0; k < T; ++k)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                dd r = wave_reduce(dd{hi[k][p], lo[k][p]});
+                if (lane == 0) red[wave][k * NP + p] = r;
+            }
+    }
     __syncthreads();
     dd r{0.0, 0.0};
     if (threadIdx.x < (uint32_t)(T * NP)) {
@@ -182,8 +185,15 @@ __device__ __forceinline__ void lattice_body(const LatticeArgs &a) {
     for (int k = 0; k < T; ++k)
 #pragma unroll
         for (int p = 0; p < NP; ++p) hi[k][p] = lo[k][p] = 0.0;
-    walk_points<Fam, Tr, D, T>(blockIdx.x * kBlock + threadIdx.x, a.n, gridDim.x * kBlock, a.n, a.inv_n, g, gs,
-                               sh + (size_t)k0 * D, prm, hi, lo);
+    const double *dls = sh + (size_t)k0 * D;
+    if constexpr (shifts_in_lds<Fam>(0)) {
+        __shared__ double staged[T * D];
+        for (uint32_t q = threadIdx.x; q < (uint32_t)(T * D); q += kBlock) staged[q] = dls[q];
+        __syncthreads();
+        dls = staged;
+    }
+    walk_points<Fam, Tr, D, T>(blockIdx.x * kBlock + threadIdx.x, a.n, gridDim.x * kBlock, a.n, a.inv_n, g, gs, dls,
+                               prm, hi, lo);
 
     __shared__ dd red[kBlock / kWave][T * NP];
     const dd r = block_reduce<T, NP>(hi, lo, red);

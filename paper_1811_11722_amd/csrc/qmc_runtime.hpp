@@ -77,9 +77,13 @@ qmc_status validate_rule(uint32_t d, uint64_t n, const uint64_t *g, uint32_t m, 
                          qmc_transform &t);
 // order in which the specialised sector code reads a polynomial's terms
 std::vector<uint32_t> horner_term_order(const std::vector<uint64_t> &codes, uint32_t d);
+// table of the deformed functor: for every entry the term of F it comes from
+// and the integer factor of the differentiation
+std::vector<std::pair<uint32_t, int>> derivative_sources(const std::vector<uint64_t> &codes, uint32_t d);
 double transform_scale(const qmc_transform &t, uint32_t d);
 LatticeLaunch find_kernel(int key_family, const qmc_transform &t, uint32_t d, uint32_t want_T, uint32_t &T_out);
 uint32_t default_tile(int key_family);
+uint32_t jit_tile(const Packed &pk, uint32_t d);
 uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu);
 void gstep_for(const uint32_t *g, uint32_t d, uint32_t n, uint64_t S, uint32_t *out);
 qmc_status ensure_buffer(void **ptr, size_t &cap, size_t bytes, const char *what);

@@ -257,3 +257,37 @@ def test_device_exp_table():
     assert float.fromhex("0x1.62e42feep-1") / 512.0 == hi
     assert int(float.hex(hi).split("p")[0].split(".")[1], 16) % (1 << 20) == 0  # 32 significant bits
     assert abs(mpmath.mpf(hi) + mpmath.mpf(lo) - mpmath.log(2) / 512) < mpmath.mpf(1e-27)
+
+
+def test_device_power_table():
+    """kPowTab is exactly what make_math_tables.py --pow writes, and its
+    entries are what qexp512, qlog512 and qphase take them for (50-digit
+    arithmetic): 2^(j/512); 1/(1/2 + (j + 1/2)/512) rounded and -512 log2 of
+    that value; the sine and cosine of 2 pi j / 256."""
+    import contextlib
+    import io
+    import mpmath
+    sys.path.insert(0, os.path.join(ROOT, "paper_1811_11722_amd", "csrc"))
+    import make_math_tables as M
+    out = io.StringIO()
+    with contextlib.redirect_stdout(out):
+        M.main_pow()
+    text = open(os.path.join(ROOT, "paper_1811_11722_amd", "csrc", "qmc_device.hpp")).read()
+    body = text[text.index("kPowTab[1536]"):]
+    body = body[body.index("{") + 1: body.index("};")]
+
+    def values(rows):
+        rows = "\n".join(line.split("//")[0] for line in rows.split("\n"))
+        return [float.fromhex(v) for v in re.findall(r"(-?0x[0-9a-fp.+-]+),", rows)]
+
+    tab = values(body)
+    assert len(tab) == 1536 and tab == values(out.getvalue())
+    with mpmath.workdps(50):
+        for j in range(512):
+            assert tab[j] == float(mpmath.power(2, mpmath.mpf(j) / 512))
+        for j in range(256):
+            ic = tab[512 + 2 * j]
+            assert ic == 1.0 / (0.5 + (j + 0.5) / 512.0)
+            assert tab[513 + 2 * j] == float(-512 * mpmath.log(mpmath.mpf(ic), 2))
+            assert tab[1024 + 2 * j] == float(mpmath.sin(2 * mpmath.pi * j / 256)) or abs(tab[1024 + 2 * j]) < 1e-30
+            assert tab[1025 + 2 * j] == float(mpmath.cos(2 * mpmath.pi * j / 256)) or abs(tab[1025 + 2 * j]) < 1e-30

@@ -411,3 +411,30 @@ def test_deform_select_rule(Q):
         plan.deform_check(Q.Params("sector", d, sector=tab))
     assert e.value.status == Q.QMC_EINVAL
     plan.close()
+
+
+@pytest.mark.parametrize("d", [1, 2, 4, 5, 7])
+@pytest.mark.parametrize("T", [1, 2])
+def test_deform_small_dimensions(Q, d, T):
+    """The eliminated Jacobian at its smallest sizes (one pivot; one with the
+    first step only) and odd ones, on a sector with monomials of degree one to
+    four (derivatives that vanish, that are constants, and Hessian entries with
+    no term), shifts on the faces of the cube (s = 0).  The bar of this file."""
+    n, m, lam = 4093, 5, 0.02
+    rng = np.random.default_rng(40 + d)
+    rows = [[0] * d, [1] + [0] * (d - 1), [2] + [0] * (d - 1), [0] * (d - 1) + [1], [1] * min(d, 4) + [0] * max(0, d - 4)]
+    if d >= 2:
+        rows += [[2, 1] + [0] * (d - 2), [0] * (d - 2) + [2, 2]]
+    exp_f = np.unique(np.array(rows, np.uint8), axis=0)
+    exp_u = np.array([[0] * d, [1] * min(d, 3) + [0] * max(0, d - 3)], np.uint8)
+    tab = synth.SectorTables(d=d, coef_u=np.array([1.0, 0.7]), exp_u=exp_u, coef_f=10.0 ** rng.uniform(-1, 1, len(exp_f)),
+                             exp_f=exp_f, nu=np.array([(i + 1) % 3 for i in range(d)], np.uint8))
+    g = O.korobov_vector(n, d, 1357)
+    sh = synth.shifts(40 + d, m, d)
+    sh[0] = 0.0
+    sh[1] = 0.5
+    _say(f"deform small d={d} T={T}")
+    res, q = _gpu(Q, d, n, g, sh, tab, lam, "baker", 0, launch=(T, 0))
+    est = _oracle_q(n, g, sh, tab, lam, "baker", 0)
+    ok, worst = _ok(q, est)
+    assert ok, worst

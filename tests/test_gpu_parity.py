@@ -635,3 +635,94 @@ def test_korobov_search_edges(Q, n, d, count):
     tol = 8 * d * 2.0 ** -53 * (1.0 + np.maximum(np.abs(ref), (1 + np.pi ** 2 / 3) ** d / n))
     assert np.all(np.abs(every - ref) <= tol), (np.abs(every - ref) / tol).max()
     assert best == every.min() and a == min(int(c) for c, p in zip(cand, every) if p == best)
+
+
+@pytest.mark.parametrize("tk,alpha", [("none", 0), ("baker", 0), ("korobov", 1), ("korobov", 6)])
+@pytest.mark.parametrize("n", [2, 3, 5, 8])
+@pytest.mark.parametrize("jit", [0, 2])
+def test_point_map_exact_at_edges(Q, tk, alpha, n, jit):
+    """f = z_1 z_2 against exact rational arithmetic at the true points
+    {j g / n + Delta}, with shifts at the edges of the point map: 0, 1/2, the
+    doubles beside 1/2 and below 1 (an unwrapped baker point crosses its fold
+    there).  A coordinate carries at most 2^-53, its map has slope at most W
+    (the largest weight) and the weight slope at most 4 alpha W, values are at
+    most W^2: 8 (1 + 4 alpha) 2 W^2 2^-53, absolute.  A point within 2^-53 of a face
+    may round onto it and wrap; both maps are continuous there except for no
+    transform, where such shifts are left out."""
+    from fractions import Fraction as Fr
+    edge = [0.0, 0.5, np.nextafter(0.5, 0), np.nextafter(0.5, 1), 0.25, 1 - 2.0 ** -53, 2.0 ** -53]
+    if tk == "none":
+        edge = [0.0, 0.5, 0.25, 0.125, 0.75, 0.375, 0.0625]
+        if n & (n - 1):
+            edge = [e + 0.03125 for e in edge]
+    m, d = 7, 2
+    sh = np.array([[edge[k], edge[(3 * k + 1) % 7]] for k in range(m)])
+    g = np.array([1, n - 1], dtype=np.uint64)
+    c = Fr(math.factorial(2 * alpha + 1), math.factorial(alpha) ** 2)
+
+    def zw(x):
+        if tk == "none":
+            return x, Fr(1)
+        if tk == "baker":
+            return 1 - abs(2 * x - 1), Fr(1)
+        u, t = x * (1 - x), x - Fr(1, 2)
+        return Fr(1, 2) + t * sum(math.comb(2 * k, k) * u ** k for k in range(alpha + 1)), c * u ** alpha
+
+    want = []
+    for k in range(m):
+        total = Fr(0)
+        for j in range(n):
+            f = Fr(1)
+            for i in range(d):
+                z, w = zw((Fr(j * int(g[i]), n) + Fr(float(sh[k, i]))) % 1)
+                f *= z * w
+            total += f
+        want.append(float(total / n))
+    one = np.ones(1)
+    tab = synth.SectorTables(d=d, coef_u=one, exp_u=np.zeros((1, d), np.uint8), coef_f=one,
+                             exp_f=np.zeros((1, d), np.uint8), nu=np.ones(d, np.uint8))
+    plan = Q.Plan(d, n, g, sh, tk, alpha)
+    plan.set_jit(jit)
+    _say(f"point map {tk}{alpha} n={n} jit={jit}")
+    _, q = plan.integrate(Q.Params("sector", d, sector=tab))
+    plan.close()
+    W = float(c / 4 ** alpha) if tk == "korobov" else 1.0 + (tk == "baker")
+    assert np.all(np.abs(q - want) <= 8 * (1 + 4 * alpha) * 2 * W ** 2 * 2.0 ** -53), np.abs(q - want).max()
+
+
+@pytest.mark.parametrize("tk,alpha", [("none", 0), ("baker", 0), ("korobov", 2)])
+@pytest.mark.parametrize("n", [2, 3, 255, 257, 8191, 8193, 262139])
+@pytest.mark.parametrize("d,jit", [(1, 0), (3, 2), (8, 2), (9, 2)])
+def test_grid_edges(Q, tk, alpha, n, d, jit):
+    """Lattice sizes around the grid's steps: one point per thread, a partial
+    last workgroup, 32 points per thread.  Positive integrands at interior
+    points (random shifts): 1e-12 as above."""
+    sh = synth.shifts(77 + d, 7, d)
+    tab = synth.sector_tables(77 + d, d, 6, 12)
+    g = np.array([(2 * i + 1) % n or 1 for i in range(d)], dtype=np.uint64)
+    _say(f"grid edges {tk}{alpha} n={n} d={d} jit={jit}")
+    _, q, est = _both(Q, "sector", d, n, g, sh, tk, alpha, jit=jit, sector=tab)
+    assert np.all(_rel(q, est.q_re) < TOL), _rel(q, est.q_re).max()
+
+
+@pytest.mark.parametrize("p", [-1.3, 0.5, 37.0, -999.5, 9.99e4])
+@pytest.mark.parametrize("f", [0.6, -0.6, 1e-9])
+def test_complex_power_phase_range(Q, p, f):
+    """U = 1, F constant, |F - i delta| near 1: the integrand is the constant
+    (F - i delta)^p, whose phase p arg runs up to 3e5.  Exact value in 50
+    digits; both the logarithm and the angle carry a few units of 2^-53, times
+    |p|: 8 (|p| + 4) 2^-53 relative."""
+    import mpmath
+    delta = float(np.sqrt(1 - f * f))
+    s = synth.SectorTables(d=1, coef_u=np.array([1.0]), exp_u=np.zeros((1, 1), np.uint8), coef_f=np.array([f]),
+                           exp_f=np.zeros((1, 1), np.uint8), nu=np.zeros(1, np.uint8), pow_u=-2.0, pow_f=p,
+                           delta_im=delta, is_complex=True)
+    with mpmath.workdps(50):
+        want = complex(mpmath.mpc(f, -delta) ** mpmath.mpf(p))
+    for jit in (0, 2):
+        plan = Q.Plan(1, 1021, np.array([1], np.uint64), synth.shifts(3, 2, 1), "baker")
+        plan.set_jit(jit)
+        _say(f"complex power p={p} f={f} jit={jit}")
+        _, q = plan.integrate(Q.Params("sector", 1, sector=s))
+        plan.close()
+        assert np.all(np.abs(q - want) <= 8 * (abs(p) + 4) * 2.0 ** -53 * abs(want)), np.abs(q - want).max()
