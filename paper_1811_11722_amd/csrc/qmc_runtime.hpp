@@ -24,6 +24,23 @@ constexpr uint32_t kMaxTile = 8;  // largest shift tile of any kernel
 
 struct qmc_plan_extra;  // batch / graph state, owned by qmc_batch.hip
 
+struct Packed {
+    std::vector<double> blob;
+    uint32_t np = 1;       // parts accumulated per shift
+    int key_family = 0;
+    bool cplx = false;     // complex sector
+    uint32_t orders = 0;   // expansion orders (>= 2: qmc_integrate_orders)
+    bool deform = false;   // contour deformation (complex result, specialised kernel only)
+    bool crossing = false; // last part: 1 where the deformed contour has Im(F - i delta) > 0
+};
+
+// The caller's parameters as bytes (every value, no pointer), to recognise the
+// same integrand in a later call by comparing contents.
+struct RawParams {
+    int family = -1;  // -1: none
+    std::vector<unsigned char> bytes;
+};
+
 }  // namespace qmc
 
 struct qmc_plan_s {
@@ -44,6 +61,12 @@ struct qmc_plan_s {
     size_t partials_cap = 0;  // in bytes
     double *h_out = nullptr;  // pinned; Q_k of every part, then the results (written by the finalize kernel)
     std::vector<double> last_blob;
+    // the last integrand: the caller's values, their packed form, and the
+    // specialised kernel found for it at a shift tile (last_fn_T, 0: none)
+    qmc::RawParams last_raw;
+    qmc::Packed last_pk;
+    hipFunction_t last_fn = nullptr;
+    uint32_t last_fn_T = 0;
     uint32_t cur_S = 0;  // thread stride that d_gstep was computed for
     qmc_launch launch{0, 0};
     uint32_t last_T = 0, last_bx = 0;
@@ -59,20 +82,13 @@ struct qmc_plan_s {
 
 namespace qmc {
 
-struct Packed {
-    std::vector<double> blob;
-    uint32_t np = 1;       // parts accumulated per shift
-    int key_family = 0;
-    bool cplx = false;     // complex sector
-    uint32_t orders = 0;   // expansion orders (>= 2: qmc_integrate_orders)
-    bool deform = false;   // contour deformation (complex result, specialised kernel only)
-    bool crossing = false; // last part: 1 where the deformed contour has Im(F - i delta) > 0
-};
-
 qmc_status fail(qmc_status s, const char *fmt, ...);
 qmc_status hip_fail(hipError_t e, const char *what);
 int device_cu_count(int dev);
 qmc_status pack_params(int family, uint32_t d, const void *params, Packed &pk);
+bool raw_same(const RawParams &raw, int family, uint32_t d, const void *params);
+bool raw_take(RawParams &raw, int family, uint32_t d, const void *params);
+qmc_status plan_pack(qmc_plan_s *p, int family, const void *params, const Packed *&pk);
 qmc_status validate_rule(uint32_t d, uint64_t n, const uint64_t *g, uint32_t m, const double *shifts,
                          qmc_transform &t);
 // order in which the specialised sector code reads a polynomial's terms

@@ -61,6 +61,7 @@ std::string tune_key(const qmc_plan_s *p, const Packed &pk, bool jit) {
 bool tune_lookup(const qmc_plan_s *p, const Packed &pk, bool jit, qmc_launch &out) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
     load_locked();
+    if (g_tune.empty()) return false;  // nothing tuned: no key to build
     auto it = g_tune.find(tune_key(p, pk, jit));
     if (it == g_tune.end()) return false;
     out = it->second;
