@@ -32,7 +32,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------- kernels
 // Design-matrix factors of dimension i in FP64:
-//   rho_j[r] = sw_j prod_{i' != i} h_{r,i'}(z_{j,i'}),  phi_j[k] = P~_k(z_{j,i}),
+//   rho_j[r] = sw_j prod_{i' != i} h_{r,i'}(z_{j,i'}),  phi_j[k] = P~_k(z_{j,i})
+// (phi only for callers that ask for it: training keeps the coordinate z_{j,i}
+// in a column of its own and the kernels below compute phi where they use it,
+// 4 bytes per point instead of 8 K), with
 // h_{r,i'}(z) = sum_k ws[r, i', k] P_k(z) on v_mfma_f64_16x16x4f64: A = the
 // Legendre values (lane l: point l % 16, degree 4 s + l / 16), B = the
 // weights.  Up to 32 ranks a wave takes 64 points at a time, each lane runs
@@ -49,7 +52,8 @@ struct CvRhoArgs {
     const float *z, *sw;    // (n, d), (n)
     const double *ws;       // W * sqrt(2k+1), (R, d, K)
     double *rho;            // (n, R)
-    double *phi;            // (n, K) (normalised)
+    double *phi;            // (n, K) (normalised), or null
+    float *zi;              // (n): the coordinate i by itself, or null
 };
 
 constexpr uint32_t kCvMaxD = 12;
@@ -94,7 +98,8 @@ __global__ __launch_bounds__(kBlock) void k_cv_rho(const CvRhoArgs a) {
                 double pk[NP];
                 legendre_raw<NP, double>(pm < a.n ? (double)zr[i] : 0.5, pk);
                 if (i == a.i) {
-                    if (pm < a.n) {
+                    if (pm < a.n && a.zi) a.zi[pm] = zr[i];
+                    if (pm < a.n && a.phi) {
 #pragma unroll
                         for (int k = 0; k < K; ++k) a.phi[(size_t)pm * K + k] = pk[k] * sqrt((double)(2 * k + 1));
                     }
@@ -177,10 +182,11 @@ __global__ __launch_bounds__(kBlock) void k_cv_rho(const CvRhoArgs a) {
 #pragma unroll
                 for (int s = 0; s < KS; ++s) fa[s] = cv_pick4(pk[4 * s], pk[4 * s + 1], pk[4 * s + 2], pk[4 * s + 3], s1, s2, s3);
                 if (i == a.i) {
+                    if (pa < a.n && lg == 0 && a.zi) a.zi[pa] = zr[i];
 #pragma unroll
                     for (int s = 0; s < KS; ++s) {
                         const uint32_t k = 4 * s + lg;
-                        if (pa < a.n && k < (uint32_t)K) a.phi[(size_t)pa * K + k] = fa[s] * sqrt((double)(2 * k + 1));
+                        if (pa < a.n && a.phi && k < (uint32_t)K) a.phi[(size_t)pa * K + k] = fa[s] * sqrt((double)(2 * k + 1));
                     }
                     continue;
                 }
@@ -222,7 +228,7 @@ __global__ __launch_bounds__(kBlock) void k_cv_rho(const CvRhoArgs a) {
 // workgroup runs one task over one contiguous range of points (grid.x), 64
 // points per round:
 //   1. the round's rho, phi go to LDS as FP32 (the next round's are loaded
-//      into registers meanwhile),
+//      into registers meanwhile; SyrkStage),
 //   2. wave w builds the BF16 fragments of points 16 w .. 16 w + 15 for the
 //      task's blocks [blo, bhi) into LDS (v_mfma_f32_32x32x16_bf16 operand
 //      layout: lane l holds column 32 b + l % 32 of points 8 (l / 32) .. +7;
@@ -237,7 +243,8 @@ struct CvSyrkTask {
 
 struct CvSyrkArgs {
     uint32_t n, splits, nslots, ntasks;
-    const double *rho, *phi;
+    const double *rho, *phi;  // (n, R), (n, K), or
+    const float *zi;          // where phi is null, the coordinate it is computed from (n)
     const CvSyrkTask *tasks;
     float *partial;  // (splits, nslots, 32, 32)
 };
@@ -323,10 +330,67 @@ __device__ __forceinline__ void syrk_store(uint32_t lane, uint32_t r0, uint32_t 
         }
 }
 
-template <int R, int K, class S>
+// A round's rho and phi on their way to LDS as FP32: loaded into registers
+// ahead by the NT threads, stored when the buffer is free.  The loads are
+// branch-free (indices clamped into the range, values from `end` on zeroed
+// when they are stored): behind a branch the compiler waits for them where
+// the paths meet instead of where they are used.  Without phi in memory
+// (ZI) the last wave computes it from the coordinate, one point per lane.
+template <int R, int K, int NT, bool ZI>
+struct SyrkStage {
+    static constexpr int NR = kSyrkPts * R / NT, NF = ZI ? 1 : (kSyrkPts * K + NT - 1) / NT;
+    static_assert(kSyrkPts == kWave && kSyrkPts * R % NT == 0, "one point per lane, whole rows");
+    double r[NR], f[NF];
+    float z;
+    __device__ __forceinline__ void load(const CvSyrkArgs &a, uint32_t base, uint32_t end, uint32_t tid) {
+        base = base < end ? base : end - 1;
+        const uint32_t m = end - base < (uint32_t)kSyrkPts ? end - base : (uint32_t)kSyrkPts;
+        const double *rho = a.rho + (size_t)base * R;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+            const uint32_t v = tid + q * NT;
+            r[q] = rho[v < m * R ? v : m * R - 1];
+        }
+        if constexpr (ZI) {
+            const uint32_t l = tid & (kWave - 1);
+            z = a.zi[base + (l < m ? l : m - 1)];
+        } else {
+            const double *phi = a.phi + (size_t)base * K;
+#pragma unroll
+            for (int q = 0; q < NF; ++q) {
+                const uint32_t w = tid + q * NT;
+                f[q] = phi[w < m * K ? w : m * K - 1];
+            }
+        }
+    }
+    __device__ __forceinline__ void store(uint32_t base, uint32_t end, uint32_t tid, float *srho, float *sphi) const {
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+            const uint32_t v = tid + q * NT;
+            srho[v] = base + v / R < end ? (float)r[q] : 0.0f;
+        }
+        if constexpr (ZI) {
+            if (tid >= NT - kWave) {
+                const uint32_t l = tid & (kWave - 1);
+                double p[K];
+                legendre_raw<K, double>((double)z, p);
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    sphi[l * K + k] = base + l < end ? (float)(p[k] * sqrt((double)(2 * k + 1))) : 0.0f;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < NF; ++q) {
+                const uint32_t w = tid + q * NT;
+                if (w < (uint32_t)(kSyrkPts * K)) sphi[w] = base + w / K < end ? (float)f[q] : 0.0f;
+            }
+        }
+    }
+};
+
+template <int R, int K, class S, bool ZI>
 __device__ __forceinline__ void syrk_task(const CvSyrkArgs &a, const CvSyrkTask &task, float *srho, float *sphi,
                                           bf16x8 *frag) {
-    constexpr int NV = (kSyrkPts * (R + K) + kBlock - 1) / kBlock;  // staged values per thread
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const uint32_t j_begin = (uint32_t)((uint64_t)a.n * blockIdx.x / a.splits);
     const uint32_t j_end = (uint32_t)((uint64_t)a.n * (blockIdx.x + 1) / a.splits);
@@ -340,32 +404,12 @@ __device__ __forceinline__ void syrk_task(const CvSyrkArgs &a, const CvSyrkTask 
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
 
-    // value v of a round: v < 64 R -> rho[p][r], else phi[p][k]
-    double nxt[NV];
-    auto load_round = [&](uint32_t base) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            const uint32_t v = tid + q * kBlock;
-            double x = 0.0;
-            if (v < (uint32_t)(kSyrkPts * R)) {
-                if (base + v / R < j_end) x = a.rho[(size_t)base * R + v];
-            } else if (v < (uint32_t)(kSyrkPts * (R + K))) {
-                const uint32_t w = v - kSyrkPts * R;
-                if (base + w / K < j_end) x = a.phi[(size_t)base * K + w];
-            }
-            nxt[q] = x;
-        }
-    };
-    if (j_begin < j_end) load_round(j_begin);
+    SyrkStage<R, K, kBlock, ZI> nxt;
+    if (j_begin < j_end) nxt.load(a, j_begin, j_end, tid);
     for (uint32_t base = j_begin; base < j_end; base += kSyrkPts) {
         __syncthreads();  // the previous round's fragments are consumed
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            const uint32_t v = tid + q * kBlock;
-            if (v < (uint32_t)(kSyrkPts * R)) srho[v] = (float)nxt[q];
-            else if (v < (uint32_t)(kSyrkPts * (R + K))) sphi[v - kSyrkPts * R] = (float)nxt[q];
-        }
-        if (base + kSyrkPts < j_end) load_round(base + kSyrkPts);
+        nxt.store(base, j_end, tid, srho, sphi);
+        nxt.load(a, base + kSyrkPts, j_end, tid);
         __syncthreads();
         {
             const uint32_t half = lane >> 5, c = lane & 31;
@@ -402,16 +446,16 @@ __device__ __forceinline__ void syrk_task(const CvSyrkArgs &a, const CvSyrkTask 
 }
 
 // S0: shapes of task type 0, S1 of type 1 (void: none); NB blocks of fragments in LDS
-template <int R, int K, class S0, class S1>
+template <int R, int K, class S0, class S1, bool ZI>
 __global__ __launch_bounds__(kBlock, 2) void k_cv_syrk(const CvSyrkArgs a) {
     constexpr int NB = R * K / 32;
     __shared__ float srho[kSyrkPts * R], sphi[kSyrkPts * K];
     __shared__ bf16x8 frag[NB * 4 * kWave];
     const CvSyrkTask task = a.tasks[blockIdx.y];
     if (task.type == 0) {
-        syrk_task<R, K, S0>(a, task, srho, sphi, frag);
+        syrk_task<R, K, S0, ZI>(a, task, srho, sphi, frag);
     } else if constexpr (!std::is_same<S1, void>::value) {
-        syrk_task<R, K, S1>(a, task, srho, sphi, frag);
+        syrk_task<R, K, S1, ZI>(a, task, srho, sphi, frag);
     }
 }
 
@@ -420,14 +464,24 @@ __global__ __launch_bounds__(kBlock, 2) void k_cv_syrk(const CvSyrkArgs a) {
 // are read and turned into fragments once for both: for the triangle of 12
 // blocks (its two halves) the features are read once in all.  All NB
 // blocks' fragments are built (wave w: 16-point group w % 4, blocks
-// w / 4, w / 4 + 2, ...).  One workgroup per CU.
-template <int R, int K, class S0, class S1>
+// w / 4, w / 4 + 2, ...).  One workgroup per CU, so nothing else fills the
+// waits: where two sets of buffers fit in LDS (all but R K = 768) the steps of
+// consecutive rounds overlap, with one barrier a round.  Bound by matrix
+// instructions and LDS reads; 1048573 points, R = 32, K = 12: 224 us with
+// three barriers a round and the waits for memory that branches around the
+// loads had caused, 175 us now (0.96 PFLOP/s in BF16).
+template <int R, int K>
+constexpr int syrk_buffers() {
+    const int one = kSyrkPts * (R + K) * 4 + (R * K / 32) * 4 * kWave * 16;
+    return 2 * one <= 160 * 1024 ? 2 : 1;
+}
+template <int R, int K, class S0, class S1, bool ZI>
 __global__ __launch_bounds__(2 * kBlock, 1) void k_cv_syrk2(const CvSyrkArgs a) {
     constexpr int NB = R * K / 32;
     constexpr uint32_t nt = 2 * kBlock;
-    constexpr int NV = (kSyrkPts * (R + K) + nt - 1) / nt;  // staged values per thread
-    __shared__ float srho[kSyrkPts * R], sphi[kSyrkPts * K];
-    __shared__ bf16x8 frag[NB * 4 * kWave];
+    constexpr int NS = syrk_buffers<R, K>();
+    __shared__ float srho[NS][kSyrkPts * R], sphi[NS][kSyrkPts * K];
+    __shared__ bf16x8 frag[NS][NB * 4 * kWave];
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, w4 = wave & 3;
     const uint32_t ti = 2 * blockIdx.y + (wave >> 2);
     const bool active = ti < a.ntasks;
@@ -444,66 +498,81 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_cv_syrk2(const CvSyrkArgs a) 
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
 
-    double nxt[NV];
-    auto load_round = [&](uint32_t base) {
+    SyrkStage<R, K, nt, ZI> nxt;
+    // the fragments of a staged round
+    auto build = [&](int b0) {
+        const float *sr = srho[b0], *sp = sphi[b0];
+        const uint32_t half = lane >> 5, c = lane & 31;
+        for (uint32_t b = wave >> 2; b < (uint32_t)NB; b += 2) {
+            const uint32_t u = 32 * b + c, k = u / R, r = u - k * R;
+            bf16x8 f;
 #pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            const uint32_t v = tid + q * nt;
-            double x = 0.0;
-            if (v < (uint32_t)(kSyrkPts * R)) {
-                if (base + v / R < j_end) x = a.rho[(size_t)base * R + v];
-            } else if (v < (uint32_t)(kSyrkPts * (R + K))) {
-                const uint32_t w = v - kSyrkPts * R;
-                if (base + w / K < j_end) x = a.phi[(size_t)base * K + w];
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t p = 16 * w4 + 8 * half + e;
+                f[e] = (__bf16)(sr[p * R + r] * sp[p * K + k]);
             }
-            nxt[q] = x;
+            frag[b0][(b * 4 + w4) * kWave + lane] = f;
         }
     };
-    if (j_begin < j_end) load_round(j_begin);
-    for (uint32_t base = j_begin; base < j_end; base += kSyrkPts) {
-        __syncthreads();  // the previous round's fragments are consumed
+    auto multiply = [&](int b0) {
+        if (!active) return;
 #pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            const uint32_t v = tid + q * nt;
-            if (v < (uint32_t)(kSyrkPts * R)) srho[v] = (float)nxt[q];
-            else if (v < (uint32_t)(kSyrkPts * (R + K))) sphi[v - kSyrkPts * R] = (float)nxt[q];
-        }
-        if (base + kSyrkPts < j_end) load_round(base + kSyrkPts);
-        __syncthreads();
-        {
-            const uint32_t half = lane >> 5, c = lane & 31;
-            for (uint32_t b = wave >> 2; b < (uint32_t)NB; b += 2) {
-                const uint32_t u = 32 * b + c, k = u / R, r = u - k * R;
-                bf16x8 f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const uint32_t p = 16 * w4 + 8 * half + e;
-                    f[e] = (__bf16)(srho[p * R + r] * sphi[p * K + k]);
+        for (int s = 0; s < 4; ++s) {
+            const bf16x8 *fr = frag[b0] + s * kWave;
+            if (type == 0) {
+                switch (w4) {
+                case 0: syrk_step<S0, 0>(fr, lane, r0, c0, acc); break;
+                case 1: syrk_step<S0, 1>(fr, lane, r0, c0, acc); break;
+                case 2: syrk_step<S0, 2>(fr, lane, r0, c0, acc); break;
+                default: syrk_step<S0, 3>(fr, lane, r0, c0, acc); break;
                 }
-                frag[(b * 4 + w4) * kWave + lane] = f;
-            }
-        }
-        __syncthreads();
-        if (active) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const bf16x8 *fr = frag + s * kWave;
-                if (type == 0) {
-                    switch (w4) {
-                    case 0: syrk_step<S0, 0>(fr, lane, r0, c0, acc); break;
-                    case 1: syrk_step<S0, 1>(fr, lane, r0, c0, acc); break;
-                    case 2: syrk_step<S0, 2>(fr, lane, r0, c0, acc); break;
-                    default: syrk_step<S0, 3>(fr, lane, r0, c0, acc); break;
-                    }
-                } else if constexpr (!std::is_same<S1, void>::value) {
-                    switch (w4) {
-                    case 0: syrk_step<S1, 0>(fr, lane, r0, c0, acc); break;
-                    case 1: syrk_step<S1, 1>(fr, lane, r0, c0, acc); break;
-                    case 2: syrk_step<S1, 2>(fr, lane, r0, c0, acc); break;
-                    default: syrk_step<S1, 3>(fr, lane, r0, c0, acc); break;
-                    }
+            } else if constexpr (!std::is_same<S1, void>::value) {
+                switch (w4) {
+                case 0: syrk_step<S1, 0>(fr, lane, r0, c0, acc); break;
+                case 1: syrk_step<S1, 1>(fr, lane, r0, c0, acc); break;
+                case 2: syrk_step<S1, 2>(fr, lane, r0, c0, acc); break;
+                default: syrk_step<S1, 3>(fr, lane, r0, c0, acc); break;
                 }
             }
+        }
+    };
+    if constexpr (NS == 2) {
+        // round t in buffer t % 2; at the top of a round its fragments are
+        // built, round t + 1 is staged and round t + 2 is in registers
+        if (j_begin < j_end) {
+            nxt.load(a, j_begin, j_end, tid);
+            nxt.store(j_begin, j_end, tid, srho[0], sphi[0]);
+            nxt.load(a, j_begin + kSyrkPts, j_end, tid);
+            __syncthreads();
+            build(0);
+            nxt.store(j_begin + kSyrkPts, j_end, tid, srho[1], sphi[1]);
+            nxt.load(a, j_begin + 2 * kSyrkPts, j_end, tid);
+            __syncthreads();
+        }
+        int cur = 0;
+        for (uint32_t base = j_begin; base < j_end; base += kSyrkPts, cur ^= 1) {
+            auto prepare = [&]() {
+                build(cur ^ 1);
+                nxt.store(base + 2 * kSyrkPts, j_end, tid, srho[cur], sphi[cur]);
+                nxt.load(a, base + 3 * kSyrkPts, j_end, tid);
+            };
+            // a SIMD's two waves (w, w + 4) take the halves of a round in
+            // opposite order
+            if (wave >= 4) prepare();
+            multiply(cur);
+            if (wave < 4) prepare();
+            __syncthreads();
+        }
+    } else {
+        if (j_begin < j_end) nxt.load(a, j_begin, j_end, tid);
+        for (uint32_t base = j_begin; base < j_end; base += kSyrkPts) {
+            __syncthreads();  // the previous round's fragments are consumed
+            nxt.store(base, j_end, tid, srho[0], sphi[0]);
+            nxt.load(a, base + kSyrkPts, j_end, tid);
+            __syncthreads();
+            build(0);
+            __syncthreads();
+            multiply(0);
         }
     }
     if (!active) return;
@@ -560,6 +629,11 @@ __global__ __launch_bounds__(kBlock) void k_cv_gather(const float *partial, uint
 // v_mfma_f64_16x16x4f64 (A[i][k] and B[k][j] at lane i (or j) + 16 k;
 // output element v of lane l at row 4 v + l / 16, column l % 16).  A wave
 // takes 16 points at a time:
+//   0. training: each lane runs the Legendre recurrence of its point l % 16
+//      and keeps the degrees of step 1's layout; step 3's comes from these
+//      through LDS.  The kernel is bound by the bytes of rho, and phi from
+//      memory would add 8 K to the 8 R of a point (1048573 points, R = 32,
+//      K = 12: 77 us with it, 64 us now, 4.3 TB/s);
 //   1. H = Phi W^T (16 points x 16 ranks per tile; A: lane l holds
 //      phi[point l % 16][4 s + l / 16], B: the weights, kept in registers),
 //      so lane l holds H at point 4 v + l / 16 and rank 16 t + l % 16;
@@ -594,7 +668,9 @@ __device__ __forceinline__ double row16_sum(double v) {
 
 struct CvPassArgs {
     uint32_t n, d, i, splits;
-    const double *rho, *phi;  // (n, R), (n, K)
+    const double *rho;        // (n, R)
+    const double *phi;        // (n, K), with the targets yd, or
+    const float *zi;          // with yf: the coordinate phi is computed from (n)
     const float *yf;          // targets (float) times y_scale, or
     double y_scale;
     const double *yd;         // targets (double), if not null
@@ -629,6 +705,17 @@ __global__ __launch_bounds__(kBlock) void k_cv_pass(const CvPassArgs a) {
     // a chunk waits on memory once.
     const uint32_t rl = li < (uint32_t)R ? li : 0;  // rank lane, clamped (R = 8)
     const uint32_t kl = li < (uint32_t)K ? li : 0;           // Legendre lane, clamped
+    constexpr uint32_t LP = 17;                              // padded row of a point's values
+    __shared__ double red[4][RT * 256 > 16 * LP ? RT * 256 : 16 * LP];
+    double *lw = red[wave];  // until the tiles are added: phi of the wave's chunk
+    const bool s1 = lg == 1, s2 = lg == 2, s3 = lg == 3;
+    double norm[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        norm[s] = s1 ? sqrt(8.0 * s + 3.0) : sqrt(8.0 * s + 1.0);
+        norm[s] = s2 ? sqrt(8.0 * s + 5.0) : norm[s];
+        norm[s] = s3 ? sqrt(8.0 * s + 7.0) : norm[s];
+    }
     for (uint32_t p0 = j0 + 16 * wave; p0 < j1; p0 += 64) {
         double rh[RT][4], y[4], fa[KS], fb[4];
 #pragma unroll
@@ -637,14 +724,30 @@ __global__ __launch_bounds__(kBlock) void k_cv_pass(const CvPassArgs a) {
 #pragma unroll
             for (int t = 0; t < RT; ++t) rh[t][v] = a.rho[(size_t)pc * R + (16 * t + rl)];
             y[v] = NORMAL ? a.yd[pc] : (double)a.yf[pc] * a.y_scale;
-            fb[v] = a.phi[(size_t)pc * K + kl];
+            if constexpr (NORMAL) fb[v] = a.phi[(size_t)pc * K + kl];
         }
-        {
-            const uint32_t p = p0 + li, pc = p < j1 ? p : j1 - 1;
+        const uint32_t pl = p0 + li < j1 ? p0 + li : j1 - 1;
+        if constexpr (!NORMAL) {
+            double pk[4 * KS];
+            legendre_raw<4 * KS, double>((double)a.zi[pl], pk);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                fa[s] = cv_pick4(pk[4 * s], pk[4 * s + 1], pk[4 * s + 2], pk[4 * s + 3], s1, s2, s3) * norm[s];
+                lw[li * LP + 4 * s + lg] = fa[s];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int v = 0; v < 4; ++v) fb[v] = lw[(4 * v + lg) * LP + kl];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        if constexpr (NORMAL) {
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
                 const uint32_t k = 4 * s + lg;
-                fa[s] = a.phi[(size_t)pc * K + (k < (uint32_t)K ? k : 0)];
+                fa[s] = a.phi[(size_t)pl * K + (k < (uint32_t)K ? k : 0)];
             }
         }
 #pragma unroll
@@ -686,7 +789,6 @@ __global__ __launch_bounds__(kBlock) void k_cv_pass(const CvPassArgs a) {
     }
     // tiles of the 4 waves, added in wave order; element v of lane l is
     // rank 16 t + 4 v + l / 16, Legendre index l % 16
-    __shared__ double red[4][RT * 256];
     __shared__ double se2[4][4];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
@@ -1577,10 +1679,15 @@ void launch_pass(const CvPassArgs &a, uint32_t blocks, hipStream_t s) {
 }
 // one task per workgroup of 4 waves when the triangle is one task, two
 // per workgroup of 8 waves otherwise (grid.y = tasks / 2)
+template <int R, int K, class S0, class S1, bool ZI>
+void launch_syrk_from(const CvSyrkArgs &a, dim3 grid, hipStream_t s) {
+    if constexpr (R * K / 32 <= 8) hipLaunchKernelGGL((k_cv_syrk<R, K, S0, S1, ZI>), grid, dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((k_cv_syrk2<R, K, S0, S1, ZI>), grid, dim3(2 * kBlock), 0, s, a);
+}
 template <int R, int K, class S0, class S1>
 void launch_syrk(const CvSyrkArgs &a, dim3 grid, hipStream_t s) {
-    if (a.ntasks == 1) hipLaunchKernelGGL((k_cv_syrk<R, K, S0, S1>), grid, dim3(kBlock), 0, s, a);
-    else hipLaunchKernelGGL((k_cv_syrk2<R, K, S0, S1>), grid, dim3(2 * kBlock), 0, s, a);
+    if (a.phi) launch_syrk_from<R, K, S0, S1, false>(a, grid, s);
+    else if (a.zi) launch_syrk_from<R, K, S0, S1, true>(a, grid, s);
 }
 
 struct CvFns {
@@ -1676,6 +1783,7 @@ struct CvTrainer {
     CvFns fn{};
     DeviceScratch s;
     float *z = nullptr, *sw = nullptr, *yw = nullptr, *partial = nullptr;
+    float *zi = nullptr;
     double *rho = nullptr, *phi = nullptr, *rpart = nullptr, *ydev = nullptr, *ws = nullptr;
     double *w64 = nullptr, *A0 = nullptr, *A = nullptr, *Aw = nullptr, *Wd = nullptr, *rdiag = nullptr;
     double *Rm = nullptr, *Mi = nullptr, *Ai = nullptr, *dl = nullptr;
@@ -1684,9 +1792,10 @@ struct CvTrainer {
     int *status = nullptr, *flag = nullptr;
     CvSyrkTask *tasks = nullptr;
 
-    // samples: allocate z, sw, yw too; features: rho, phi and the Gram's
-    // and right-hand side's partial sums
-    qmc_status init(uint32_t n_, uint32_t d_, uint32_t R_, uint32_t K_, bool samples, bool features) {
+    // samples: allocate z, sw, yw and the solved coordinate's column too;
+    // features: rho and the Gram's and right-hand side's partial sums;
+    // keep_phi: phi in memory (else computed from the column where it is used)
+    qmc_status init(uint32_t n_, uint32_t d_, uint32_t R_, uint32_t K_, bool samples, bool features, bool keep_phi) {
         n = n_;
         d = d_;
         R = R_;
@@ -1714,8 +1823,9 @@ struct CvTrainer {
             return r;
         };
         if ((samples && ((st = take((size_t)n * d * 4, z)) || (st = take((size_t)n * 4, sw)) ||
-                         (st = take((size_t)n * 4, yw)))) ||
-            (features && ((st = take((size_t)n * R * 8, rho)) || (st = take((size_t)n * K * 8, phi)) ||
+                         (st = take((size_t)n * 4, yw)) || (st = take((size_t)n * 4, zi)))) ||
+            (keep_phi && (st = take((size_t)n * K * 8, phi))) ||
+            (features && ((st = take((size_t)n * R * 8, rho)) ||
                           (st = take((size_t)splits * nslots * 4096, partial)) ||
                           (st = take((size_t)rsplits * (F + 1) * 8, rpart)) || (st = take((size_t)n * 8, ydev)))) ||
             (st = take((size_t)R * d * K * 8, ws)) || (st = take((size_t)R * d * K * 8, w64)) ||
@@ -1751,13 +1861,13 @@ struct CvTrainer {
     }
 
     void features(uint32_t i, hipStream_t st) {
-        const CvRhoArgs ra{n, d, i, z, sw, ws, rho, phi};
+        const CvRhoArgs ra{n, d, i, z, sw, ws, rho, phi, zi};
         fn.rho(ra, std::min<uint32_t>(rblocks, 1024), st);
     }
 
     // A0 = sum_j a~_j a~_j^T (BF16 MFMA, FP32 accumulation per split, FP64 over splits)
     void gram(hipStream_t st) {
-        const CvSyrkArgs ga{n, splits, nslots, ntasks, rho, phi, tasks, partial};
+        const CvSyrkArgs ga{n, splits, nslots, ntasks, rho, phi, zi, tasks, partial};
         fn.syrk(ga, dim3(splits, gy), st);
         hipLaunchKernelGGL(k_cv_gather, dim3(nslots * 1024 / kBlock), dim3(kBlock), 0, st, (const float *)partial,
                            splits, nslots, R, K, A0);
@@ -1768,7 +1878,7 @@ struct CvTrainer {
     // equations' own right-hand side: use_w false, yd set)
     void rhs(uint32_t i, bool use_w, const float *yf, double y_scale, const double *yd, const int *fl,
              hipStream_t st) {
-        const CvPassArgs pa{n, d, i, rsplits, rho, phi, yf, y_scale, yd, use_w ? w64 : nullptr, fl, rpart};
+        const CvPassArgs pa{n, d, i, rsplits, rho, phi, zi, yf, y_scale, yd, use_w ? w64 : nullptr, fl, rpart};
         fn.pass(pa, rsplits, st);
         hipLaunchKernelGGL(k_cv_rhs_reduce, dim3((F + 1 + kBlock / kWave - 1) / (kBlock / kWave)), dim3(kBlock), 0,
                            st, (const double *)rpart, rsplits, F + 1, fl, b);
@@ -1872,7 +1982,7 @@ qmc_status qmc_cv_train(qmc_plan_t p, qmc_family family, const void *params, uin
     if ((st = plan_upload_params(p, pk.blob))) return st;
 
     CvTrainer t;
-    if ((st = t.init(n, d, R, K, true, true))) return st;
+    if ((st = t.init(n, d, R, K, true, true, false))) return st;
     hipStream_t stream = p->stream;
     struct Events {
         hipEvent_t t0 = nullptr, t1 = nullptr;
@@ -2026,7 +2136,7 @@ qmc_status qmc_cv_features(uint32_t n, uint32_t d, uint32_t R, uint32_t K, uint3
     for (size_t t = 0; t < (size_t)R * d * K; ++t)
         if (!std::isfinite(w[t])) return fail(QMC_EINVAL, "W not finite");
     CvTrainer t;
-    if ((st = t.init(n, d, R, K, true, true)) || (st = t.set_weights(w))) return st;
+    if ((st = t.init(n, d, R, K, true, true, true)) || (st = t.set_weights(w))) return st;
     hipError_t e;
     if ((e = hipMemcpy(t.z, z, (size_t)n * d * 4, hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(t.sw, sw, (size_t)n * 4, hipMemcpyHostToDevice)) != hipSuccess)
@@ -2044,7 +2154,7 @@ qmc_status qmc_cv_normal(uint32_t n, uint32_t R, uint32_t K, const double *rho, 
     qmc_status st = check_step_sizes(n, 1, R, K, 0);
     if (st) return st;
     CvTrainer t;
-    if ((st = t.init(n, 1, R, K, false, true))) return st;
+    if ((st = t.init(n, 1, R, K, false, true, true))) return st;
     hipError_t e;
     if ((e = hipMemcpy(t.rho, rho, (size_t)n * R * 8, hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(t.phi, phi, (size_t)n * K * 8, hipMemcpyHostToDevice)) != hipSuccess ||
@@ -2078,7 +2188,7 @@ qmc_status qmc_cv_solve(uint32_t R, uint32_t K, const double *gram, const double
     for (uint32_t u = 0; u < F; ++u)
         if (!std::isfinite(rhs[u])) return fail(QMC_EINVAL, "right-hand side not finite");
     CvTrainer t;
-    if ((st = t.init(1, 1, R, K, false, false))) return st;
+    if ((st = t.init(1, 1, R, K, false, false, false))) return st;
     hipError_t e;
     if ((e = hipMemcpy(t.A0, gram, (size_t)F * F * 8, hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(t.b, rhs, (size_t)F * 8, hipMemcpyHostToDevice)) != hipSuccess)
@@ -2109,7 +2219,7 @@ qmc_status qmc_cv_als_step(uint32_t n, uint32_t d, uint32_t R, uint32_t K, uint3
     for (size_t t = 0; t < (size_t)R * d * K; ++t)
         if (!std::isfinite(w_in[t])) return fail(QMC_EINVAL, "W not finite");
     CvTrainer t;
-    if ((st = t.init(n, d, R, K, true, true)) || (st = t.set_weights(w_in))) return st;
+    if ((st = t.init(n, d, R, K, true, true, false)) || (st = t.set_weights(w_in))) return st;
     hipError_t e;
     if ((e = hipMemcpy(t.z, z, (size_t)n * d * 4, hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(t.sw, sw, (size_t)n * 4, hipMemcpyHostToDevice)) != hipSuccess ||

@@ -93,7 +93,8 @@ __device__ __forceinline__ void walk_points(uint32_t j, uint32_t j1, uint32_t S,
         nms[i] = n - gs[i];
     }
     // scalar shifts leave no scalar operand for 1/n in the point's FMA
-    const double rn = shifts_in_lds<Fam>(0) ? inv_n : vreg_const(inv_n);
+    constexpr bool kStaged = !Reload && shifts_in_lds<Fam>(0);
+    const double rn = kStaged ? inv_n : vreg_const(inv_n);
 #pragma unroll 1
     while (more()) {
         double s[T][NP];
@@ -115,7 +116,7 @@ __device__ __forceinline__ void walk_points(uint32_t j, uint32_t j1, uint32_t S,
                 asm volatile("" : "+s"(dl));  // keep the shift loads inside the loop
             }
             // staged shifts are read anew at every point, not hoisted
-            if constexpr (shifts_in_lds<Fam>(0)) asm volatile("" ::: "memory");
+            if constexpr (kStaged) asm volatile("" ::: "memory");
             double x[T][D];
 #pragma unroll
             for (int k = 0; k < T; ++k)

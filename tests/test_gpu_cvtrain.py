@@ -286,3 +286,40 @@ def test_als_step_reaches_ridge_minimum(Q, d, R, K, n):
         mask = np.ones(d, bool)
         mask[i] = False
         assert np.array_equal(W2[:, mask, :], W[:, mask, :])
+
+
+@pytest.mark.parametrize("R,K", [(32, 12), (32, 16), (64, 12), (16, 8)])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 130, 193, 16449])
+def test_step_computes_phi_as_features_do(Q, R, K, n):
+    """A step never stores phi: the Gram and the pass compute it from the
+    coordinate, over rounds of 64 points and chunks of 16 with remainders.
+    Against the same quantities from the stored phi of cv_features: lam is
+    ridge / F times the Gram's trace, so it must be the same bit for bit;
+    the correction is (G + lam)^-1 (A^T (y - A w) - lam w) up to the
+    rounding of that right-hand side (sums of n and F terms in FP64) times
+    the inverse's norm and the solve's own error (as above)."""
+    d, i, ridge, F = 3, 1, 1e-2, R * K
+    rng = np.random.default_rng(1000 * R + 10 * K + n)
+    z, sw, yw = rng.random((n, d), np.float32), rng.random(n, np.float32), rng.random(n, np.float32)
+    W = _init_factors(R + K, R, d, K)
+    _say(f"cv step phi R={R} K={K} n={n}")
+    rho, phi = Q.cv_features(z, sw, W, i)
+    y = yw.astype(np.float64)
+    G, _, _ = Q.cv_normal(rho, phi, y)
+    W0, lam = Q.cv_als_step(z, sw, yw, 1.0, W, i, ridge, refine=0)
+    trace = 0.0
+    for u in range(F):
+        trace += G[u, u]
+    assert lam == ridge * trace / F + 1e-300
+    A = (rho[:, :, None] * phi[:, None, :]).reshape(n, F)
+    w = W[:, i, :].reshape(F)
+    b = A.T @ (y - A @ w) - lam * w
+    eb = (n + F + 40) * U64 * (np.abs(A).T @ (np.abs(y) + np.abs(A) @ np.abs(w)) + lam * np.abs(w))
+    M = G + lam * np.eye(F)
+    ev = np.linalg.eigvalsh(M)
+    x = np.linalg.solve(M, b)
+    got = (W0[:, i, :] - W[:, i, :]).reshape(F)
+    err = np.linalg.norm(got - x)
+    bound = np.linalg.norm(eb) / ev[0] + 12 * F * ev[-1] / ev[0] * U64 * np.linalg.norm(x) + 2 * U64 * np.linalg.norm(w)
+    print(f"  |x - x_ref| {err:.3g} (bound {bound:.3g}, |x| {np.linalg.norm(x):.3g})")
+    assert err <= bound
