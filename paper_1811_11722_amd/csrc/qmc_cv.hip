@@ -822,19 +822,43 @@ __global__ __launch_bounds__(kBlock) void k_cv_pass(const CvPassArgs a) {
     }
 }
 
-// b[u] = sum over splits of the partials: one wave per column, lanes take
-// splits lane, lane + 64, ... in order, then a fixed butterfly over the lanes
-// (F counts the extra entry of the pass: R K + 1 columns)
-__global__ __launch_bounds__(kBlock) void k_cv_rhs_reduce(const double *part, uint32_t splits, uint32_t F,
-                                                         const int *flag, double *b) {
-    if (flag && *flag) return;
-    const uint32_t u = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    if (u >= F) return;
+// b[u] = sum over splits of the partials: a workgroup takes kRhsCols adjacent
+// columns (64 bytes of a split's row), kWave threads per column; thread l
+// of a column takes splits l, l + 64, ... in order, then the threads are
+// added pairwise (l and l + 32, l + 16, ...).  Bound by the latency of the
+// partials, all of a thread's in flight together: 1024 splits of 385 columns
+// took 6.5 us with a wave per column (every lane another row), 4.6 us now,
+// of which an empty launch takes 4.  (F counts the extra entry of the pass:
+// R K + 1 columns.)
+constexpr uint32_t kRhsCols = 8;
+__global__ __launch_bounds__(kRhsCols * kWave) void k_cv_rhs_reduce(const double *part, uint32_t splits, uint32_t F,
+                                                                   const int *flag, double *b) {
+    const int stop = flag ? *flag : 0;
+    const uint32_t c = threadIdx.x % kRhsCols, l = threadIdx.x / kRhsCols, u = blockIdx.x * kRhsCols + c;
+    const uint32_t uc = u < F ? u : F - 1;
+    __shared__ double red[kWave][kRhsCols];
     double s = 0.0;
-    for (uint32_t sp = lane; sp < splits; sp += kWave) s += part[(size_t)sp * F + u];
+    for (uint32_t s0 = l; s0 < splits; s0 += 16 * kWave) {
+        double v[16];
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) b[u] = s;
+        for (int k = 0; k < 16; ++k) {
+            const uint32_t sp = s0 + k * kWave;
+            v[k] = part[(size_t)(sp < splits ? sp : s0) * F + uc];
+        }
+        if (stop) return;
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (s0 + k * kWave < splits) s += v[k];
+    }
+    if (stop) return;
+    red[l][c] = s;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t o = kWave / 2; o > 0; o >>= 1) {
+        if (l < o) red[l][c] += red[l + o][c];
+        __syncthreads();
+    }
+    if (l == 0 && u < F) b[u] = red[0][c];
 }
 
 // ------------------------------------------------------------ the solve
@@ -1084,7 +1108,9 @@ __global__ __launch_bounds__(kFactorThreads) void k_cv_factor(const CvFactorArgs
 // 1 / sqrt(pivot) (hardware reciprocal square root and two Newton steps)
 // and the lanes take the rank-1 update with the column's entries broadcast
 // through LDS (the entry of the next pivot's row by readlane, which is
-// quicker).  The same operations on the identity rows are column-wise
+// quicker, so that the next pivot's chain runs while the broadcasts come
+// back: a step of F = 384 took 14.9 us, 13.1 us now, of which an empty
+// launch takes 4).  The same operations on the identity rows are column-wise
 // forward substitution, so lanes 32 + c end with column c of W = L_pp^-1
 // at no extra latency.  The factor goes to A (lower triangle), 1 / L_uu to
 // rdiag, W_p to Wd; a non-positive pivot sets *status = -1 and the launches
@@ -1122,8 +1148,8 @@ __device__ void chol_diag_block(double *D, double *cb, uint32_t c0, uint32_t slo
     for (int c = 0; c < B; ++c) x[c] = fac ? D[r * kCholDP + c] : (c == (int)r ? 1.0 : 0.0);
     bool bad = false;
     double rinv = 0.0;
-#pragma unroll
-    for (int q = 0; q < B; ++q) {
+    // scales column q by 1 / sqrt(pivot)
+    auto scale = [&](int q) {
         const double piv = readlane_d(x[q], q);
         bad = bad || !(piv > 0.0);
         const double pv = piv > 0.0 ? piv : 1.0;
@@ -1133,10 +1159,21 @@ __device__ void chol_diag_block(double *D, double *cb, uint32_t c0, uint32_t slo
         const bool own = lane == (uint32_t)q;
         rinv = own ? rq : rinv;
         x[q] = own ? pv * rq : x[q] * rq;
-        cb[q * kWave + lane] = x[q];  // unconditional: a branch here lets the updates sink
-        if (q + 1 < B) x[q + 1] = fma(-x[q], readlane_d(x[q], q + 1), x[q + 1]);
+    };
+    scale(0);
 #pragma unroll
-        for (int c = q + 2; c < B; ++c) x[c] = fma(-x[q], cb[q * kWave + c], x[c]);
+    for (int q = 0; q < B; ++q) {
+        cb[q * kWave + lane] = x[q];  // unconditional: a branch here lets the updates sink
+        double v[B];
+#pragma unroll
+        for (int c = q + 2; c < B; ++c) v[c] = cb[q * kWave + c];
+        // the next column's pivot chain while the broadcasts come back
+        if (q + 1 < B) {
+            x[q + 1] = fma(-x[q], readlane_d(x[q], q + 1), x[q + 1]);
+            scale(q + 1);
+        }
+#pragma unroll
+        for (int c = q + 2; c < B; ++c) x[c] = fma(-x[q], v[c], x[c]);
         // one column at a time: reads hoisted across columns would take
         // hundreds of registers
         __builtin_amdgcn_sched_barrier(0);
@@ -1169,14 +1206,14 @@ __global__ __launch_bounds__(kWave) void k_cv_chol_diag0(const CvCholArgs a) {
     __syncthreads();
     double lam = 0.0;
     if (lane == 0) {
-        // in index order (F is a multiple of 32), 8 reads in flight
+        // in index order (F is a multiple of 32), 32 reads in flight
         double t = 0.0;
-        for (uint32_t u = 0; u < F; u += 8) {
-            double v[8];
+        for (uint32_t u = 0; u < F; u += 32) {
+            double v[32];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = sdiag[u + k];
+            for (int k = 0; k < 32; ++k) v[k] = sdiag[u + k];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) t += v[k];
+            for (int k = 0; k < 32; ++k) t += v[k];
         }
         lam = a.ridge * t / F + 1e-300;
         *a.lam = lam;
@@ -1195,8 +1232,8 @@ __global__ __launch_bounds__(kWave) void k_cv_chol_diag0(const CvCholArgs a) {
 // Block (I, J), I > p >= J, of the inverse's substitution in step p (see
 // above): wave w takes the 16 x 16 tiles (w >> 1, w & 1) of L_Ip, M_pJ and
 // R_IJ.
-__device__ void chol_inverse_tile(const CvCholArgs &a, uint32_t p, uint32_t I, uint32_t J, double *LI, double *LM,
-                                  uint32_t tid) {
+__device__ void chol_inverse_tile(const CvCholArgs &a, uint32_t p, uint32_t I, uint32_t J, int status, double *LI,
+                                  double *LM, uint32_t tid) {
     constexpr uint32_t B = kCholB, DP = kCholDP;
     const uint32_t F = a.F, lane = tid & (kWave - 1), wave = tid / kWave;
     const uint32_t li = lane & 15, lg = lane >> 4, h = wave >> 1, j2 = wave & 1;
@@ -1216,6 +1253,7 @@ __device__ void chol_inverse_tile(const CvCholArgs &a, uint32_t p, uint32_t I, u
         wa[s] = W[(16 * h + li) * B + k];
         rr[s] = p == J ? (k == 16 * j2 + li ? 1.0 : 0.0) : a.Rm[(size_t)(c0 + k) * F + B * J + 16 * j2 + li];
     }
+    if (status < 0) return;
     cv_d4 xl = cv_d4{0.0, 0.0, 0.0, 0.0}, xm = xl;
 #pragma unroll
     for (int s = 0; s < (int)B / 4; ++s) {
@@ -1245,7 +1283,7 @@ __device__ void chol_inverse_tile(const CvCholArgs &a, uint32_t p, uint32_t I, u
 }
 
 __global__ __launch_bounds__(256) void k_cv_chol_step(const CvCholArgs a, uint32_t p) {
-    if (*a.status < 0) return;
+    const int status = *a.status;  // looked at once the block's loads are on their way
     constexpr uint32_t B = kCholB, DP = kCholDP;
     __shared__ double LI[B * DP], LJ[B * DP], D[B * DP], cb[B * kWave];
     const uint32_t F = a.F, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -1253,7 +1291,7 @@ __global__ __launch_bounds__(256) void k_cv_chol_step(const CvCholArgs a, uint32
     const uint32_t NB = F / B, m = NB - 1 - p, ntrail = m * (m + 1) / 2;
     if (blockIdx.x >= ntrail) {
         const uint32_t t = blockIdx.x - ntrail;
-        chol_inverse_tile(a, p, p + 1 + t / (p + 1), t % (p + 1), LI, LJ, tid);
+        chol_inverse_tile(a, p, p + 1 + t / (p + 1), t % (p + 1), status, LI, LJ, tid);
         return;
     }
     // block t -> (ti, tj), tj <= ti, of the trailing triangle
@@ -1286,6 +1324,7 @@ __global__ __launch_bounds__(256) void k_cv_chol_step(const CvCholArgs a, uint32
         aj[s] = src[(size_t)(B * J + 16 * h + li) * F + c0 + 4 * s + lg];
         w[s] = W[(16 * j2 + li) * B + 4 * s + lg];
     }
+    if (status < 0) return;
     cv_d4 xi = cv_d4{0.0, 0.0, 0.0, 0.0}, xj = xi;
 #pragma unroll
     for (int s = 0; s < (int)B / 4; ++s) {
@@ -1894,8 +1933,8 @@ struct CvTrainer {
              hipStream_t st) {
         const CvPassArgs pa{n, d, i, rsplits, rho, phi, zi, yf, y_scale, yd, use_w ? w64 : nullptr, fl, rpart};
         fn.pass(pa, rsplits, st);
-        hipLaunchKernelGGL(k_cv_rhs_reduce, dim3((F + 1 + kBlock / kWave - 1) / (kBlock / kWave)), dim3(kBlock), 0,
-                           st, (const double *)rpart, rsplits, F + 1, fl, b);
+        hipLaunchKernelGGL(k_cv_rhs_reduce, dim3((F + kRhsCols) / kRhsCols), dim3(kRhsCols * kWave), 0, st,
+                           (const double *)rpart, rsplits, F + 1, fl, b);
     }
 
     // L L^T = A0 + lam I (one launch per panel of 32 columns, then the
