@@ -323,3 +323,22 @@ def test_step_computes_phi_as_features_do(Q, R, K, n):
     bound = np.linalg.norm(eb) / ev[0] + 12 * F * ev[-1] / ev[0] * U64 * np.linalg.norm(x) + 2 * U64 * np.linalg.norm(w)
     print(f"  |x - x_ref| {err:.3g} (bound {bound:.3g}, |x| {np.linalg.norm(x):.3g})")
     assert err <= bound
+
+
+@pytest.mark.parametrize("R,K", [(32, 12), (32, 16), (16, 8), (8, 4)])
+@pytest.mark.parametrize("d,n", [(1, 65), (2, 1), (2, 257), (3, 200000), (12, 300)])
+def test_features_edges(Q, d, R, K, n):
+    """The loop over the other dimensions loads one dimension ahead, the next
+    round's first at the end: no other dimension, one, the most; one point, a
+    remainder, several rounds per workgroup.  Bounds as above."""
+    rng = np.random.default_rng(d * 100 + R)
+    z, sw = rng.random((n, d), np.float32), rng.random(n, np.float32)
+    W = _init_factors(d + R, R, d, K)
+    for i in sorted({0, d // 2, d - 1}):
+        _say(f"cv features edges d={d} R={R} K={K} n={n} i={i}")
+        rho_g, phi_g = Q.cv_features(z, sw, W, i)
+        rho, phi, env = O.cv_features(z, sw, W, i)
+        k = np.arange(K)
+        B_rho, B_phi = _feature_bounds(d, K, env, k)
+        assert np.all(np.abs(rho_g - rho) <= B_rho * env)
+        assert np.all(np.abs(phi_g - phi) <= B_phi[None, :] * np.sqrt(2 * k + 1)[None, :])
