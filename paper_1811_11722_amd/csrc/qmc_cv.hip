@@ -2003,6 +2003,14 @@ qmc_status check_step_sizes(uint32_t n, uint32_t d, uint32_t R, uint32_t K, uint
     return QMC_OK;
 }
 
+// the plan's first shift as SampleMap's table
+void sample_shift(const qmc_plan_s *p, double *out) {
+    for (uint32_t i = 0; i < p->d; ++i) {
+        const double v = p->shifts[i];
+        out[i] = p->tr.kind != QMC_T_BAKER ? v : (v < 0.5 ? v + 0.5 : v - 0.5);
+    }
+}
+
 }  // namespace
 
 }  // namespace qmc
@@ -2059,7 +2067,7 @@ qmc_status qmc_cv_train(qmc_plan_t p, qmc_family family, const void *params, uin
         sa.d = d;
         sa.inv_n = p->inv_n;
         sa.g = p->d_g;
-        sa.shift = p->d_shifts;  // the plan's first shift
+        sample_shift(p, sa.shift);
         sa.params = p->d_params;
         sa.z = t.z;
         sa.sw = t.sw;
@@ -2165,7 +2173,7 @@ qmc_status qmc_cv_samples(qmc_plan_t p, qmc_family family, const void *params, u
     sa.d = d;
     sa.inv_n = p->inv_n;
     sa.g = p->d_g;
-    sa.shift = p->d_shifts;
+    sample_shift(p, sa.shift);
     sa.params = p->d_params;
     sa.z = (float *)s.ptr[0];
     sa.sw = (float *)s.ptr[1];

@@ -71,6 +71,16 @@ __device__ __forceinline__ double recip(double b) {
     return fma_(r, fma_(e, e, e), r);
 }
 
+// The same by two Newton steps (the training sampler's arithmetic, see
+// sector_sample): the last bit differs now and then.
+__device__ __forceinline__ double recip_newton(double b) {
+    double r = __builtin_amdgcn_rcp(b);
+    double e = fma_(-b, r, 1.0);
+    r = fma_(r, e, r);
+    e = fma_(-b, r, 1.0);
+    return fma_(r, e, r);
+}
+
 // r_k = 1 / b_k for T values from one reciprocal (v_rcp_f64 issues at a
 // quarter of the FP64 rate): prefix products, the reciprocal of their total,
 // then two multiplies back per value.  The caller guarantees that every
@@ -91,8 +101,9 @@ __device__ __forceinline__ void recip_tile(const double (&b)[T], double (&r)[T])
 }
 
 // a / b via the refined reciprocal and one residual correction.
+template <bool Newton = false>
 __device__ __forceinline__ double divide(double a, double b) {
-    const double r = recip(b);
+    const double r = Newton ? recip_newton(b) : recip(b);
     const double q = a * r;
     const double res = fma_(-b, q, a);
     return fma_(res, r, q);
@@ -1522,13 +1533,14 @@ constexpr double kLnOf512 = 0.0013538030870311431;  // ln x = kLnOf512 qlog512(x
 // |t| <= tan(pi/8), where atan(t) = t + t^3 P(t^2) with P of degree 10.  The
 // octant and quadrant are restored with pi/4, pi/2 - a, pi - a and the sign
 // of y.
+template <bool Newton = false>
 __device__ __forceinline__ double qatan2(double y, double x) {
     constexpr double kTanPi8 = 0x1.a827999fcef32p-2;
     constexpr double kPi4 = 0x1.921fb54442d18p-1, kPi2 = 0x1.921fb54442d18p+0, kPi = 0x1.921fb54442d18p+1;
     const double ax = __builtin_fabs(x), ay = __builtin_fabs(y);
     const double n = __builtin_fmin(ax, ay), d = __builtin_fmax(ax, ay);
     const bool big = n > kTanPi8 * d;
-    const double t = divide(big ? n - d : n, big ? n + d : d);
+    const double t = divide<Newton>(big ? n - d : n, big ? n + d : d);
     const double s = t * t;
     double p = -0x1.3a31b1c0fd3b7p-6;
     p = fma_(p, s, 0x1.4162c02b1dda3p-5);

@@ -433,8 +433,10 @@ static std::string sector_structure(const std::vector<double> &blob, uint32_t d,
 }
 
 // Source of the specialised functor FamJit; `structure` receives a
-// canonical description of what the code depends on.
-static std::string functor_source(const std::vector<double> &blob, uint32_t d, bool cplx, std::string &structure) {
+// canonical description of what the code depends on.  finish: the function
+// that forms a value from the polynomials (sector_sample for the sampler).
+static std::string functor_source(const std::vector<double> &blob, uint32_t d, bool cplx, std::string &structure,
+                                  const char *finish = "sector_finish") {
     const uint32_t nu = (uint32_t)word(blob, 0), nf = (uint32_t)word(blob, 1);
     // expansion orders (flag 4): three words after the F codes (eps_u,
     // eps_f, count); other blobs may carry other data there
@@ -521,7 +523,7 @@ static std::string functor_source(const std::vector<double> &blob, uint32_t d, b
           << ">(mono, U[k], F[k], flags, pow_u, pow_f, delta, cp[" << eps_at << "], cp[" << eps_at + 1
           << "], v[k]);\n";
     else
-        s << "            sector_finish<" << (cplx ? "true" : "false")
+        s << "            " << finish << "<" << (cplx ? "true" : "false")
           << ">(mono, U[k], F[k], flags, pow_u, pow_f, delta, v[k]);\n";
     s << "        }\n    }\n};\n";
     return s.str();
@@ -852,7 +854,7 @@ hipFunction_t jit_sample_kernel(const std::vector<double> &blob, uint32_t d, con
     hipFunction_t fn = nullptr;
     if (jit_lookup(key.str(), fn, err)) return fn;
     std::string structure;
-    const std::string fam = functor_source(blob, d, cplx, structure);
+    const std::string fam = functor_source(blob, d, cplx, structure, "sector_sample");
     std::ostringstream ne, src;
     ne << "qmc::k_cv_sample<qmc::FamJit, qmc::" << transform_type(tr) << ", " << d << ">";
     src << "#include \"qmc_cv.hpp\"\nnamespace qmc {\n" << fam << "template __global__ void k_cv_sample<FamJit, "

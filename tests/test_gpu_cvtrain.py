@@ -20,6 +20,8 @@ the oracle's FP64 / long-double computation of the same quantity:
 Shapes: workload 4 (d = 8, R = 32, K = 12, F = 384), workload 5's model
 (d = 10, R = 64, K = 12, F = 768) and a small R < 32 case.
 """
+import dataclasses
+import hashlib
 import math
 import os
 import sys
@@ -342,3 +344,55 @@ def test_features_edges(Q, d, R, K, n):
         B_rho, B_phi = _feature_bounds(d, K, env, k)
         assert np.all(np.abs(rho_g - rho) <= B_rho * env)
         assert np.all(np.abs(phi_g - phi) <= B_phi[None, :] * np.sqrt(2 * k + 1)[None, :])
+
+
+# First 16 hex digits of the SHA-256 of z, sw and yw (bytes, one after
+# another) per configuration below.
+SAMPLE_BITS = {
+    "baker": "eae3000bfdcb6d57",
+    "baker_complex": "8b69922fc3532030",
+    "baker_pow": "84f88ba7863fe81b",
+    "korobov1_small": "8af2932da83bf660",
+    "korobov2": "f1a888c55ebab988",
+    "korobov3_complex": "47bcd8a1c61bc37c",
+    "none": "3a2d72bd9a54cb50",
+    "sidi3": "895cf5fe0e7a322a",
+}
+
+
+def _sample_config(name):
+    """(plan arguments, sector, parts): every map the sampler has, U^-2 by
+    reciprocal and U by its power, real and complex, an odd size and one below a
+    workgroup, shifts on the maps' folds."""
+    tk, alpha, d, n, cplx, pow_u = {
+        "korobov2": ("korobov", 2, 8, 65521, False, None), "baker": ("baker", 0, 6, 65521, False, None),
+        "baker_pow": ("baker", 0, 5, 32749, False, -1.5), "none": ("none", 0, 3, 65521, False, None),
+        "sidi3": ("sidi", 3, 4, 16381, False, None), "korobov3_complex": ("korobov", 3, 12, 16381, True, None),
+        "baker_complex": ("baker", 0, 10, 32749, True, -2.5), "korobov1_small": ("korobov", 1, 2, 97, False, -0.5)}[name]
+    tab = synth.sector_tables(500 + d, d, 12, 30, complex_kinematics=cplx)
+    if pow_u is not None:
+        tab = dataclasses.replace(tab, pow_u=pow_u)
+    sh = synth.shifts(500 + d, 2, d, stream=3)
+    sh[0, 0], sh[0, -1] = 0.5, np.nextafter(0.5, 0)
+    return (d, n, O.korobov_vector(n, d, 17364 % n), sh, tk, alpha), tab, 2 if cplx else 1
+
+
+def _sample_bits(Q, name):
+    args, tab, parts = _sample_config(name)
+    plan = Q.Plan(*args)
+    h = hashlib.sha256()
+    for part in range(parts):
+        for a in plan.cv_samples(Q.Params("sector", args[0], sector=tab), part):
+            h.update(np.ascontiguousarray(a).tobytes())
+    return h.hexdigest()[:16]
+
+
+@pytest.mark.parametrize("name", sorted(SAMPLE_BITS))
+def test_samples_keep_their_bits(Q, name):
+    """The samples are the same bits as ever: a fit amplifies a change of
+    rounding in them (one FP32 unit of one large target moves the factors by
+    1e-8 and more), so their arithmetic is pinned apart from the estimate's.
+    The digests are of the kernels before the estimate's power functions and
+    points were rewritten."""
+    _say(f"cv sample bits {name}")
+    assert _sample_bits(Q, name) == SAMPLE_BITS[name]
