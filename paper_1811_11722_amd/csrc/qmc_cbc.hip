@@ -150,6 +150,8 @@ constexpr int kCbcTw = 4096;          // entries of the step twiddle table exp(-
 constexpr uint32_t kCbcFinal = 1024;  // finalists summed directly; more fall back to the direct search
 constexpr uint32_t kCbcUpd = 256;     // workgroups of k_cbc_advance (partial sums of p)
 
+constexpr double two_pi2 = 2.0 * 3.141592653589793 * 3.141592653589793;
+
 struct CbcState {
     uint32_t count;     // finalists of the component at hand
     uint32_t overflow;  // 1 + the component whose finalists did not fit (0: none)
@@ -260,7 +262,7 @@ template <int LOG1, int LOG2>
 __global__ __launch_bounds__(kCbcColThreads) void k_cbc_col(const CbcFftArgs a) {
     constexpr int M1 = 1 << LOG1, M2 = 1 << LOG2, CW = cbc_cols(LOG1);
     __shared__ double2 s[M1 * CW];
-    const uint32_t c0 = blockIdx.x * CW;
+    const uint32_t c0 = blockIdx.x * CW, stop = a.state->overflow;  // looked at behind the loads
     if (blockIdx.x == 0 && threadIdx.x == 0) a.state->count = 0;
     for (uint32_t e = threadIdx.x; e < (uint32_t)(M1 * CW); e += kCbcColThreads) {
         const uint32_t t = (e / CW) * M2 + c0 + e % CW;
@@ -273,6 +275,7 @@ __global__ __launch_bounds__(kCbcColThreads) void k_cbc_col(const CbcFftArgs a) 
         }
         s[e] = make_double2(v, 0.0);
     }
+    if (stop) return;
     __syncthreads();
     cbc_fft<LOG1, CW, kCbcColThreads, false>(s, a.tw);
     for (uint32_t e = threadIdx.x; e < (uint32_t)(M1 * CW); e += kCbcColThreads) {
@@ -285,9 +288,10 @@ template <int LOG1, int LOG2>
 __global__ __launch_bounds__(kCbcRowThreads) void k_cbc_row(const CbcFftArgs a) {
     constexpr int M2 = 1 << LOG2;
     __shared__ double2 s[M2];
-    const uint32_t k1 = blockIdx.x;
+    const uint32_t k1 = blockIdx.x, stop = a.state->overflow;
     double2 *row = a.work + (size_t)k1 * M2;
     for (uint32_t e = threadIdx.x; e < (uint32_t)M2; e += kCbcRowThreads) s[e] = row[e];
+    if (stop) return;
     __syncthreads();
     cbc_fft<LOG2, 1, kCbcRowThreads, false>(s, a.tw);
     if (!a.prod) {  // the spectrum of B2 itself
@@ -308,9 +312,10 @@ template <int LOG1, int LOG2>
 __global__ __launch_bounds__(kCbcColThreads) void k_cbc_col_inv(const CbcFftArgs a) {
     constexpr int M1 = 1 << LOG1, M2 = 1 << LOG2, CW = cbc_cols(LOG1);
     __shared__ double2 s[M1 * CW];
-    const uint32_t c0 = blockIdx.x * CW;
+    const uint32_t c0 = blockIdx.x * CW, stop = a.state->overflow;
     for (uint32_t e = threadIdx.x; e < (uint32_t)(M1 * CW); e += kCbcColThreads)
         s[e] = a.work[(size_t)(e / CW) * M2 + c0 + e % CW];
+    if (stop) return;
     __syncthreads();
     cbc_fft<LOG1, CW, kCbcColThreads, true>(s, a.tw);
     double lo = __builtin_inf();
@@ -360,6 +365,7 @@ struct CbcSelectArgs {
 
 __global__ __launch_bounds__(kBlock) void k_cbc_select(const CbcSelectArgs a) {
     __shared__ double red[3][kBlock / kWave];
+    if (a.state->overflow) return;
     double lo = __builtin_inf(), s1 = 0.0, s2 = 0.0;
     for (uint32_t i = threadIdx.x; i < a.nmin; i += kBlock) lo = __builtin_fmin(lo, a.vmin[i]);
     for (uint32_t i = threadIdx.x; i < kCbcUpd; i += kBlock) {
@@ -400,7 +406,8 @@ __global__ __launch_bounds__(kBlock) void k_cbc_select(const CbcSelectArgs a) {
 
 // Direct sums of the finalists.  A workgroup owns one tile of kCbcTile points
 // of one slice (the tiles of k_cbc_eval with `slices` slices of jchunk
-// points), each thread one of its groups of 8, and walks the finalists.
+// points), each thread one of its groups of 8, and walks the finalists
+// (blockIdx.y, blockIdx.y + gridDim.y, ...).
 __global__ __launch_bounds__(kBlock) void k_cbc_exact(const CbcArgs a, uint32_t tiles, const CbcState *state) {
     static_assert(kCbcTile == 8 * kBlock, "one group of 8 per thread");
     __shared__ dd red[kBlock / kWave];
@@ -412,7 +419,8 @@ __global__ __launch_bounds__(kBlock) void k_cbc_exact(const CbcArgs a, uint32_t 
 #pragma unroll
     for (uint32_t u = 0; u < 8; ++u) p[u] = u < cnt ? a.prod[first + u] : 0.0;
     const double w6 = 1.0 + a.w / 6.0;
-    const uint32_t nf = min(state->count, kCbcFinal);
+    // finalists that do not fit are left to the direct search
+    const uint32_t nf = state->overflow || state->count > kCbcFinal ? 0u : state->count;
     for (uint32_t f = blockIdx.y; f < nf; f += gridDim.y) {
         const uint32_t c = a.cand[f];
         uint32_t idx = cnt ? (uint32_t)(((uint64_t)first * c) % a.n) : 0u;
@@ -485,12 +493,13 @@ __global__ __launch_bounds__(1024) void k_cbc_choose(const double2 *partial, uin
 }
 
 // k_cbc_update with the chosen component, and the sums of p and p^2 (j >= 1)
+// (z: where k_cbc_choose left it, or null for the component zv)
 __global__ __launch_bounds__(kBlock) void k_cbc_advance(double *prod, uint32_t n, uint32_t jend, double inv_n,
-                                                        const uint32_t *z, double w, const CbcState *state,
-                                                        double2 *psum) {
+                                                        const uint32_t *z, uint32_t zv, double w,
+                                                        const CbcState *state, double2 *psum) {
     __shared__ double red[2][kBlock / kWave];
     if (state->overflow) return;
-    const uint32_t c = *z;
+    const uint32_t c = z ? *z : zv;
     double s1 = 0.0, s2 = 0.0;
     for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < jend; j += kCbcUpd * kBlock) {
         const uint32_t idx = (uint32_t)(((uint64_t)j * c) % n);
@@ -530,7 +539,8 @@ void cbc_launch_fft(const CbcFftArgs &a, bool forward_only) {
         hipLaunchKernelGGL((k_cbc_col_inv<LOG1, LOG2>), dim3(cols), dim3(kCbcColThreads), 0, nullptr, a);
 }
 
-// log2 of the transform length: the smallest power of two >= 2N - 1 = n - 2
+// log2 of the transform length: the smallest power of two >= 2N - 1 = n - 2.
+// The bound on the work (n/2 candidates x n <= 2^44) keeps n below 2^23.
 constexpr int kCbcLogMin = 14, kCbcLogMax = 23;
 int cbc_log(uint64_t n) {
     int l = kCbcLogMin;
@@ -593,6 +603,39 @@ uint64_t primitive_root(uint64_t n) {
 // is 2^14 points there), the direct one 335, 404, 538, 909 us.
 constexpr uint64_t kScreenMin = 1000;
 
+// How far apart the errors of a component's candidates lie, to within a
+// factor of a few: the products of its weight and the largest one before it
+// over n^2.  The share of the candidates within the tie width of the best
+// follows it: 0.1 % at 1e-11, 1 % at 1e-12, 20 to 25 % at 2e-13, 73 % at 2e-14,
+// 93 % at 2e-15 (n = 2039, 4099, 16381).  Many ties are too many finalists, and
+// then the component is summed directly after all.  So:
+// - below kTieSure, where no screening pays, a component is not screened if
+//   the direct search is cheap (below kTieDirect points 50 to 300 us a
+//   component, the screening 40 to 60 us); nor with equal errors (0), nor
+//   after a component with a wider spread that had too many ties;
+// - between kTieSure and kTieMaybe it is screened and the host looks at the
+//   outcome before it enqueues the next;
+// - above, every component is enqueued ahead;
+// - where all candidates fit the finalists' list (n < 2048), screened and direct
+//   components are not mixed: the direct search of one takes 40 us there, no
+//   more than the buffers and tables of the screening.
+// Trailing zero weights, or weights of 1e-9, at n = 4099, d = 10: 0.80 ms (13 ms
+// when every component was screened first and all behind it enqueued again
+// after each that had too many ties; 0.82 ms by direct sums alone); at n = 16381
+// 1.00, 13.2 and 1.11 ms.
+constexpr double kTieSure = 5e-13, kTieMaybe = 1e-11;
+constexpr uint64_t kTieDirect = 32768;
+
+double cbc_spread(const std::vector<double> &gam, uint32_t c, uint64_t n) {
+    const double w = two_pi2 * gam[c], top = two_pi2 * *std::max_element(gam.begin(), gam.begin() + c);
+    return w / (double)n * (top / (double)n);
+}
+
+// tied: the largest spread that had too many ties so far
+bool cbc_unscreened(double spread, double tied, uint64_t n) {
+    return spread <= tied || (spread < kTieSure && n < kTieDirect);
+}
+
 uint64_t gcd_u64(uint64_t a, uint64_t b) {
     while (b) {
         const uint64_t r = a % b;
@@ -638,10 +681,16 @@ extern "C" qmc_status qmc_cbc_search(uint64_t n, uint32_t d, const double *gamma
                         (double)(n / 2) * (double)n);
         // screened search (above): prime n from kScreenMin up
         const std::vector<uint64_t> pf = prime_factors(n);
-        screen = n >= kScreenMin && pf.size() == 1 && pf[0] == n;
+        screen = n >= kScreenMin && pf.size() == 1 && pf[0] == n && cbc_log(n) <= kCbcLogMax;
+        const bool prime = screen;
+        if (screen && d > 1) {
+            uint32_t count = 0;
+            for (uint32_t c = 1; c < d; ++c) count += !cbc_unscreened(cbc_spread(gam, c, n), 0.0, n);
+            screen = n / 2 > kCbcFinal ? count > 0 : count == d - 1;
+        }
         if (!screen) {
             for (uint64_t c = 1; c <= n / 2; ++c)
-                if (gcd_u64(c, n) == 1) cs.push_back((uint32_t)c);
+                if (prime || gcd_u64(c, n) == 1) cs.push_back((uint32_t)c);
             if (cs.empty()) cs.push_back(1u);
         }
     }
@@ -659,7 +708,6 @@ extern "C" qmc_status qmc_cbc_search(uint64_t n, uint32_t d, const double *gamma
     const uint32_t slices = std::min(max_slices, std::max(1u, (want + bx - 1) / bx));
     const uint32_t nb = (jend + kBlock - 1) / kBlock;
     const double inv_n = 1.0 / (double)n;
-    const double two_pi2 = 2.0 * 3.141592653589793 * 3.141592653589793;
     DeviceScratch s;
     qmc_status st;
 
@@ -785,55 +833,86 @@ extern "C" qmc_status qmc_cbc_search(uint64_t n, uint32_t d, const double *gamma
         const uint32_t sl = first ? sl1 : slices, ch = first ? ch1 : chs, tl = first ? t1 : ts;
         const double w = two_pi2 * gam[comp];
         const CbcArgs a{(uint32_t)n, jend, 0, ch, inv_n, w, prod, list, fpart};
-        hipLaunchKernelGGL(k_cbc_exact, dim3(sl * tl, first ? 1 : 4), dim3(kBlock), 0, nullptr, a, tl,
-                           (const CbcState *)state);
+        // usually one or two finalists; enough workgroups for many where a
+        // lattice is a few tiles
+        const uint32_t gy = first ? 1u : std::min(64u, std::max(4u, 512u / (sl * tl)));
+        hipLaunchKernelGGL(k_cbc_exact, dim3(sl * tl, gy), dim3(kBlock), 0, nullptr, a, tl, (const CbcState *)state);
         hipLaunchKernelGGL(k_cbc_choose, dim3(1), dim3(1024), 0, nullptr, (const double2 *)fpart, sl * tl, (uint32_t)n,
                            inv_n, w, (const double *)prod, (const uint32_t *)list, state, comp, d_z, d_e2);
     };
-    auto advance = [&](uint32_t comp) {
+    auto advance = [&](uint32_t comp, bool chosen) {
         hipLaunchKernelGGL(k_cbc_advance, dim3(kCbcUpd), dim3(kBlock), 0, nullptr, prod, (uint32_t)n, jend, inv_n,
-                           (const uint32_t *)(d_z + comp), two_pi2 * gam[comp], (const CbcState *)state, psum);
+                           chosen ? (const uint32_t *)(d_z + comp) : nullptr, chosen ? 0u : (uint32_t)z_out[comp],
+                           two_pi2 * gam[comp], (const CbcState *)state, psum);
     };
     exact_step(0);
-    advance(0);
+    advance(0, true);
     {
         CbcFftArgs fb = fa;  // the spectrum of B2, left where the products read it
         fb.prod = nullptr;
         fb.work = (double2 *)(base + o_spec);
         if (d > 1) cbc_fft_pass(log, fb, true);
     }
-    uint32_t comp = 1, from = 0;  // next component to enqueue, first one not yet returned
-    for (;;) {
-        for (uint32_t c = comp; c < d; ++c) {
-            cbc_fft_pass(log, fa, false);
-            const CbcSelectArgs sa{(uint32_t)n, N, cbc_col_groups(log), two_pi2 * gam[c], tol, fa.value, fa.vmin, prod,
-                                   psum, perm, list, state};
-            hipLaunchKernelGGL(k_cbc_select, dim3((N + kBlock - 1) / kBlock), dim3(kBlock), 0, nullptr, sa);
-            exact_step(c);
-            advance(c);
-        }
+    uint32_t from = 0;  // first component not yet returned
+    uint32_t over = 0;  // 1 + the component that had too many finalists (0: none)
+    auto fetch = [&](uint32_t end) -> qmc_status {
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch CBC kernels");
         if ((e = hipMemcpy(&res, state, sizeof res, hipMemcpyDeviceToHost)) != hipSuccess)
             return hip_fail(e, "cbc download");
-        const uint32_t done = res.state.overflow ? res.state.overflow - 1 : d;
-        for (uint32_t c = from; c < done; ++c) {
-            z_out[c] = res.z[c];
-            e2_out[c] = res.e2[c];
+        over = res.state.overflow;
+        const uint32_t done = over ? over - 1 : end;
+        for (; from < done; ++from) {
+            z_out[from] = res.z[from];
+            e2_out[from] = res.e2[from];
         }
-        if (done == d) return QMC_OK;
-        // too many candidates within the slack (weights near zero make them
-        // all alike) or values that are not finite: this component directly
-        if ((st = direct(done, prod))) return st;
-        const uint32_t z32 = (uint32_t)z_out[done];
+        return QMC_OK;
+    };
+    double tied = 0.0;
+    auto spread = [&](uint32_t c) { return cbc_spread(gam, c, n); };
+    auto unscreened = [&](uint32_t c) { return cbc_unscreened(spread(c), tied, n); };
+    bool ahead = false;  // launches whose outcome the host has not waited for
+    // component c by direct sums (weights near zero make too many candidates
+    // alike; values that are not finite end the search there)
+    auto directly = [&](uint32_t c) -> qmc_status {
+        if ((st = direct(c, prod))) return st;
         const CbcState clear{0, 0};
-        if ((e = hipMemcpy(d_z + done, &z32, 4, hipMemcpyHostToDevice)) != hipSuccess ||
-            (e = hipMemcpy(state, &clear, sizeof clear, hipMemcpyHostToDevice)) != hipSuccess)
+        if (over && (e = hipMemcpy(state, &clear, sizeof clear, hipMemcpyHostToDevice)) != hipSuccess)
             return hip_fail(e, "cbc upload");
-        advance(done);
-        comp = from = done + 1;
-        if (comp == d) {
-            if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "cbc synchronize");
-            return QMC_OK;
+        over = 0;
+        advance(c, false);
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch CBC update");
+        from = c + 1;
+        ahead = true;
+        return QMC_OK;
+    };
+    for (uint32_t comp = 1; comp < d || from < d;) {
+        if (comp < d && !unscreened(comp)) {
+            bool look = false;
+            while (!look && comp < d && !unscreened(comp)) {
+                cbc_fft_pass(log, fa, false);
+                const CbcSelectArgs sa{(uint32_t)n, N, cbc_col_groups(log), two_pi2 * gam[comp], tol, fa.value,
+                                       fa.vmin, prod, psum, perm, list, state};
+                hipLaunchKernelGGL(k_cbc_select, dim3((N + kBlock - 1) / kBlock), dim3(kBlock), 0, nullptr, sa);
+                exact_step(comp);
+                advance(comp, true);
+                look = N > kCbcFinal && spread(comp) < kTieMaybe;
+                ++comp;
+            }
+        }
+        if (from < comp) {
+            if ((st = fetch(comp))) return st;
+            ahead = false;
+        }
+        if (over) {
+            comp = over - 1;
+            if (comp) tied = std::max(tied, spread(comp));
+            if ((st = directly(comp))) return st;
+            ++comp;
+        } else if (comp < d && unscreened(comp)) {
+            if ((st = directly(comp))) return st;
+            ++comp;
         }
     }
+    if (ahead && (e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "cbc synchronize");
+    return QMC_OK;
 }

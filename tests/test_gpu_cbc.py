@@ -103,3 +103,36 @@ def test_cbc_screened_equals_direct(Q, n, d, weights):
     zd, e2d = Q.cbc_search(n, d, gamma=gam, cand=np.arange(1, n // 2 + 1, dtype=np.uint64))
     assert list(z) == list(zd), (z, zd)
     assert np.all(np.abs(e2 - e2d) <= 2 * 2.0 ** -53 * (1 + np.abs(e2d))), np.abs(e2 - e2d).max()
+
+
+@pytest.mark.parametrize("n", [1009, 2039, 4099, 16381, 40009])
+@pytest.mark.parametrize("weights", ["zeros", "some_zeros", "1e-7", "1e-10", "falling", "alternating", "rising"])
+def test_cbc_tied_candidates(Q, n, weights):
+    """Small weights make many candidates tie, which no screening separates:
+    some components go to the direct search at once, some after a look, and
+    screened ones follow.  Same vectors as the direct search (the candidates as
+    a list), and no slower than twice its time (the searches alternate; medians
+    of five)."""
+    import time
+    d = 8
+    gam = {"zeros": np.r_[1.0, np.zeros(d - 1)], "some_zeros": np.array([1, 0, 1, 1, 0, 0, 1, 0.0]),
+           "1e-7": np.r_[1.0, np.full(d - 1, 1e-7)], "1e-10": np.r_[1.0, np.full(d - 1, 1e-10)],
+           "falling": 10.0 ** (-2.0 * np.arange(d)), "alternating": np.tile([1.0, 1e-12], d // 2),
+           "rising": 10.0 ** np.arange(-2.0 * d + 2, 1.0, 2.0)}[weights]
+    n = _prime(n, -1)
+    cand = np.arange(1, n // 2 + 1, dtype=np.uint64)
+    _say(f"cbc ties n={n} {weights}")
+    times = [[], []]
+    for _ in range(5):
+        for k, c in enumerate((None, cand)):
+            t = time.perf_counter()
+            got = Q.cbc_search(n, d, gamma=gam, cand=c)
+            times[k].append(time.perf_counter() - t)
+            if c is None:
+                z, e2 = got
+            else:
+                assert list(z) == list(got[0]), (z, got[0])
+                assert np.all(np.abs(e2 - got[1]) <= 2 * 2.0 ** -53 * (1 + np.abs(got[1])))
+    full, listed = (float(np.median(v)) for v in times)
+    print(f"  {1e6 * full:.0f} us, as a list {1e6 * listed:.0f} us")
+    assert full <= 2 * listed
