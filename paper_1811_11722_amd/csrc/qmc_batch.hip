@@ -70,6 +70,7 @@ struct BatchCtx {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     uint32_t blocks = 0;
+    uint64_t ran = 0;  // number of the last run that filled h_q (0: none)
     ~BatchCtx() {
         if (stream) (void)hipStreamSynchronize(stream);
         if (exec) (void)hipGraphExecDestroy(exec);
@@ -89,6 +90,7 @@ std::mutex g_batch_mu;
 // qmc_batch_stats: table-driven contexts built, their graph launches,
 // specialised graphs captured, their launches (under g_batch_mu)
 uint64_t g_stats[4] = {0, 0, 0, 0};
+uint64_t g_runs = 0;  // runs that filled some context's h_q (under g_batch_mu)
 std::vector<std::unique_ptr<BatchCtx>> g_batch;
 constexpr size_t kMaxContexts = 8;
 
@@ -744,6 +746,7 @@ qmc_status qmc_integrate_batch(uint32_t count, const qmc_plan_t *plans, qmc_fami
         if (st) return st;
         if (p0->timing) (void)hipEventRecord(p0->ev1, c->stream);
         if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return hip_fail(e, "batch results");
+        c->ran = ++g_runs;
         if (p0->timing) {
             float ms = 0.f;
             if (hipEventElapsedTime(&ms, p0->ev0, p0->ev1) == hipSuccess) {
@@ -777,14 +780,17 @@ qmc_status qmc_batch_stats(uint64_t *out) {
 qmc_status qmc_batch_per_shift(uint32_t count, const qmc_plan_t *plans, double *const *per_shift) {
     if (!plans || !per_shift) return fail(QMC_EINVAL, "null argument");
     std::lock_guard<std::mutex> lock(g_batch_mu);
-    for (auto &x : g_batch) {
-        if (x->plans.size() != count || !std::equal(x->plans.begin(), x->plans.end(), plans)) continue;
-        for (uint32_t i = 0; i < count; ++i)
-            if (per_shift[i])
-                std::memcpy(per_shift[i], x->h_q + x->hs[i].q_off, (size_t)x->hs[i].m * x->np * sizeof(double));
-        return QMC_OK;
-    }
-    return fail(QMC_EINVAL, "no batch ran with these plans");
+    // several contexts hold these plans when their parameters or options changed
+    const BatchCtx *last = nullptr;
+    for (auto &x : g_batch)
+        if (x->ran > (last ? last->ran : 0) && x->plans.size() == count &&
+            std::equal(x->plans.begin(), x->plans.end(), plans))
+            last = x.get();
+    if (!last) return fail(QMC_EINVAL, "no batch ran with these plans");
+    for (uint32_t i = 0; i < count; ++i)
+        if (per_shift[i])
+            std::memcpy(per_shift[i], last->h_q + last->hs[i].q_off, (size_t)last->hs[i].m * last->np * sizeof(double));
+    return QMC_OK;
 }
 
 qmc_status qmc_batch_autotune(uint32_t count, const qmc_plan_t *plans, qmc_family family, const void *const *params,
