@@ -241,8 +241,8 @@ qmc_status qmc_korobov_search(uint64_t n, uint32_t d, const uint64_t *cand, uint
    (tile_points lattice points times one shift tile) ordered longest first,
    one work list per dimension, and run by one kernel launch per dimension:
    persistent workgroups that loop over the list, or one workgroup per tile
-   taking tiles in list order (schedule); the dimensions' launches run on
-   parallel chains.  When every plan has the same d, n
+   taking tiles in list order (schedule); the dimensions' launches of a
+   sector batch run on parallel chains.  When every plan has the same d, n
    and m and tile_points is 0, the plans instead run as instances of one
    lattice-kernel launch (with the first plan's qmc_plan_set_launch
    configuration, if any).  When use_graph is set, the launch sequence is

@@ -6,11 +6,9 @@
 // into tiles of tile_points lattice points times one shift tile, orders the
 // tiles longest first (a cost model per plan: points times an evaluation
 // cost from d and the polynomial sizes) and captures {one kernel per
-// dimension on four parallel chains, per-plan finalize} into a HIP graph that
-// later calls with the same plans and parameters replay.  One dimension after
-// another, each launch ended with a thin last wave of workgroups: 250 sectors
-// of d = 2 .. 9 at n = 16381, m = 16 took 1.24 ms, 0.94 ms on chains.  The comparison mode launches each
-// plan's own lattice and finalize kernels instead, all on one stream with a
+// dimension, for sectors on four parallel chains, per-plan finalize} into a HIP
+// graph that later calls with the same plans and parameters replay.  The
+// comparison mode launches each plan's own lattice and finalize kernels instead, all on one stream with a
 // single synchronisation at the end.
 #include <algorithm>
 #include <cmath>
@@ -31,12 +29,48 @@ std::map<BatchKey, BatchLaunch> &batch_registry() {
 
 namespace {
 
+// Sector batches launch their dimensions on parallel chains, Genz batches one
+// after another.  The sector kernels wait on scalar loads, so two dimensions'
+// kernels fill each other's gaps; the Genz kernels issue without a gap and only
+// their last waves overlap, while a captured graph with four chains takes 0.2 ms
+// more to make than one with one, which a call with new parameters pays.  us a
+// call, repeated / with new parameters:
+//                                            four chains     one
+// 250 sectors of d = 2 .. 9, n = 16381, m = 16  653 / 2045    929 / 2040
+//  60 sectors, n = 65521, m = 17                658 / 1483    920 / 1468
+//  30 sectors, n = 3229, m = 16                  84 /  663    132 /  525
+//   8 sectors, n = 2039, m = 16                  55 /  564     67 /  372
+//  32 peaks of d = 2 .. 6, n = 65521, m = 8      86 /  586    105 /  392
+// 200 peaks, n = 4093, m = 8                     92 /  640    103 /  450
 constexpr size_t kBatchChains = 4;
+
+// The chains beside the context's stream.  Making three streams and four events
+// takes 0.15 ms, so the contexts of a device share one set, kept while any of
+// them lives: batches run one at a time (under g_batch_mu), and a captured graph
+// holds no stream.
+struct BatchSides {
+    hipStream_t side[kBatchChains - 1] = {};
+    hipEvent_t fork = nullptr, join[kBatchChains - 1] = {};
+    hipError_t make() {
+        hipError_t e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
+        for (size_t k = 0; k < kBatchChains - 1 && e == hipSuccess; ++k)
+            if ((e = hipStreamCreateWithFlags(&side[k], hipStreamNonBlocking)) == hipSuccess)
+                e = hipEventCreateWithFlags(&join[k], hipEventDisableTiming);
+        return e;
+    }
+    ~BatchSides() {
+        if (fork) (void)hipEventDestroy(fork);
+        for (size_t k = 0; k < kBatchChains - 1; ++k) {
+            if (join[k]) (void)hipEventDestroy(join[k]);
+            if (side[k]) (void)hipStreamDestroy(side[k]);
+        }
+    }
+};
 
 struct BatchCtx {
     std::vector<qmc_plan_s *> plans;
     std::vector<std::vector<double>> blobs;
-    std::vector<RawParams> raw;  // the callers' values the blobs were packed from
+    RawParams raw;  // the callers' values the blobs were packed from
     int key_family = 0;
     uint32_t np = 1, T = 4, tile_points = 0;
     uint32_t requested_tile_points = 0;  // the caller's option (0 = default): part of the context's key
@@ -50,10 +84,8 @@ struct BatchCtx {
         uint32_t tile_begin, ntiles;
     };
     std::vector<Group> groups;  // one launch per dimension
-    // the groups run on parallel chains (stream, then side): one dimension's
-    // last workgroups leave room that the next one's fill
-    hipStream_t side[kBatchChains - 1] = {};
-    hipEvent_t fork = nullptr, join[kBatchChains - 1] = {};
+    size_t chains = 1;
+    std::shared_ptr<BatchSides> sides;  // more than one chain
     // uniform batches (every plan with the same d, n and m): one launch of the
     // lattice kernel with the plans as instances along grid.y
     bool uniform = false;
@@ -77,11 +109,6 @@ struct BatchCtx {
         if (graph) (void)hipGraphDestroy(graph);
         if (h_q) (void)hipHostFree(h_q);
         if (h_res) (void)hipHostFree(h_res);
-        if (fork) (void)hipEventDestroy(fork);
-        for (size_t k = 0; k < kBatchChains - 1; ++k) {
-            if (join[k]) (void)hipEventDestroy(join[k]);
-            if (side[k]) (void)hipStreamDestroy(side[k]);
-        }
         if (stream) (void)hipStreamDestroy(stream);
     }
 };
@@ -135,10 +162,11 @@ qmc_status build_uniform(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, c
     if ((uint64_t)count * c.ltiles > 65535) return fail(QMC_EUNSUPPORTED, "too many instances for one launch");
     c.lbx = grid_x(n, count * c.ltiles, c.device, p0->launch.blocks_per_cu ? p0->launch.blocks_per_cu : 8);
     size_t pstride = 0;
-    std::vector<std::vector<double>> blobs;
-    for (auto &b : pk) {
-        blobs.push_back(table_blob(b, p0->d));
-        pstride = std::max(pstride, blobs.back().size());
+    std::vector<std::vector<double>> tables(count);
+    std::vector<const std::vector<double> *> blobs(count);
+    for (uint32_t i = 0; i < count; ++i) {
+        blobs[i] = &table_blob(pk[i], d, tables[i]);
+        pstride = std::max(pstride, blobs[i]->size());
     }
     std::vector<uint32_t> g((size_t)count * d), gs((size_t)count * d);
     std::vector<double> sh((size_t)count * rows * d), prm(count * pstride, 0.0);
@@ -147,7 +175,7 @@ qmc_status build_uniform(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, c
         gstep_for(plans[i]->g.data(), d, n, (uint64_t)c.lbx * kBlock, &gs[(size_t)i * d]);
         const std::vector<double> ps = padded_shifts(plans[i]->shifts, m, d, rows, plans[i]->tr);
         std::copy(ps.begin(), ps.end(), sh.begin() + (size_t)i * rows * d);
-        std::copy(blobs[i].begin(), blobs[i].end(), prm.begin() + (size_t)i * pstride);
+        std::copy(blobs[i]->begin(), blobs[i]->end(), prm.begin() + (size_t)i * pstride);
         BatchSector s{};
         s.n = n;
         s.d = d;
@@ -253,7 +281,7 @@ qmc_status build_ctx(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, const
     c.tile_points = tile_points;
 
     std::vector<uint32_t> g, gs;
-    std::vector<double> sh, prm;
+    std::vector<double> sh, prm, table;
     struct Work {
         double cost;
         uint32_t d;
@@ -282,7 +310,7 @@ qmc_status build_ctx(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, const
         gs.insert(gs.end(), step.begin(), step.end());
         const std::vector<double> psh = padded_shifts(p->shifts, p->m, p->d, (p->m + T - 1) / T * T, p->tr);
         sh.insert(sh.end(), psh.begin(), psh.end());
-        const std::vector<double> tb = table_blob(pk[i], p->d);
+        const std::vector<double> &tb = table_blob(pk[i], p->d, table);
         prm.insert(prm.end(), tb.begin(), tb.end());
         const uint32_t ktiles = (p->m + T - 1) / T;
         const double cpp = plan_cost(c.key_family, p->d, pk[i].blob) * T;
@@ -349,13 +377,17 @@ qmc_status build_ctx(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, const
     c.fargs.q = c.h_q;
     c.fargs.res = c.h_res;
     c.blocks = (uint32_t)device_cu_count(c.device) * 8;
-    const size_t sides = std::min(kBatchChains, c.groups.size()) - 1;
-    if (sides && (e = hipEventCreateWithFlags(&c.fork, hipEventDisableTiming)) != hipSuccess)
-        return hip_fail(e, "hipEventCreate");
-    for (size_t k = 0; k < sides; ++k)
-        if ((e = hipStreamCreateWithFlags(&c.side[k], hipStreamNonBlocking)) != hipSuccess ||
-            (e = hipEventCreateWithFlags(&c.join[k], hipEventDisableTiming)) != hipSuccess)
-            return hip_fail(e, "batch chains");
+    const bool sector = c.key_family == QMC_F_SECTOR || c.key_family == kFamSectorComplex;
+    if (sector) c.chains = std::min(kBatchChains, c.groups.size());
+    if (c.chains > 1) {
+        static std::map<int, std::weak_ptr<BatchSides>> shared;
+        c.sides = shared[c.device].lock();
+        if (!c.sides) {
+            c.sides = std::make_shared<BatchSides>();
+            if ((e = c.sides->make()) != hipSuccess) return hip_fail(e, "batch chains");
+            shared[c.device] = c.sides;
+        }
+    }
     return QMC_OK;
 }
 
@@ -367,9 +399,10 @@ hipError_t enqueue_batch(BatchCtx &c) {
     }
     // the persistent workgroups draw their tiles from a counter per group
     hipError_t e = c.persistent ? launch_zero_u32(c.args.counter, (uint32_t)c.groups.size(), c.stream) : hipSuccess;
-    const size_t chains = std::min(kBatchChains, c.groups.size());
-    if (chains > 1 && e == hipSuccess) e = hipEventRecord(c.fork, c.stream);
-    for (size_t k = 1; k < chains && e == hipSuccess; ++k) e = hipStreamWaitEvent(c.side[k - 1], c.fork, 0);
+    const size_t chains = c.chains;
+    BatchSides *sd = c.sides.get();
+    if (chains > 1 && e == hipSuccess) e = hipEventRecord(sd->fork, c.stream);
+    for (size_t k = 1; k < chains && e == hipSuccess; ++k) e = hipStreamWaitEvent(sd->side[k - 1], sd->fork, 0);
     for (size_t gi = 0; gi < c.groups.size() && e == hipSuccess; ++gi) {
         BatchArgs a = c.args;
         a.tiles = c.args.tiles + c.groups[gi].tile_begin;
@@ -377,12 +410,12 @@ hipError_t enqueue_batch(BatchCtx &c) {
         a.counter = c.args.counter + gi;
         const uint32_t blocks = std::min<uint32_t>(c.blocks, a.ntiles);
         const size_t k = gi % chains;
-        e = c.groups[gi].fn(a, blocks, c.persistent, k ? c.side[k - 1] : c.stream);
+        e = c.groups[gi].fn(a, blocks, c.persistent, k ? sd->side[k - 1] : c.stream);
     }
     for (size_t k = 1; k < chains; ++k) {
         // joined also after a failed launch, so that a capture can end
-        const hipError_t r = hipEventRecord(c.join[k - 1], c.side[k - 1]);
-        const hipError_t w = r == hipSuccess ? hipStreamWaitEvent(c.stream, c.join[k - 1], 0) : r;
+        const hipError_t r = hipEventRecord(sd->join[k - 1], sd->side[k - 1]);
+        const hipError_t w = r == hipSuccess ? hipStreamWaitEvent(c.stream, sd->join[k - 1], 0) : r;
         if (e == hipSuccess) e = w;
     }
     if (e == hipSuccess) e = launch_finalize_batch(c.fargs, (uint32_t)c.plans.size(), c.stream);
@@ -433,10 +466,11 @@ bool same_ctx(const BatchCtx &c, uint32_t count, const qmc_plan_t *plans, const 
 // 0.3 us (Genz) to 1.2 us (sectors) per plan, comparing the bytes 0.1 us.
 bool same_raw(const BatchCtx &c, uint32_t count, const qmc_plan_t *plans, int family, const void *const *params,
               uint32_t requested_tile_points, int persistent) {
-    if (c.raw.size() != count || !same_shape(c, count, plans, requested_tile_points, persistent)) return false;
+    if (!same_shape(c, count, plans, requested_tile_points, persistent)) return false;
+    size_t at = 0;
     for (uint32_t i = 0; i < count; ++i)
-        if (!raw_same(c.raw[i], family, plans[i]->d, params[i])) return false;
-    return true;
+        if (!raw_match(c.raw, at, family, plans[i]->d, params[i])) return false;
+    return at == c.raw.bytes.size();
 }
 
 }  // namespace
@@ -700,8 +734,8 @@ qmc_status qmc_integrate_batch(uint32_t count, const qmc_plan_t *plans, qmc_fami
         fresh->persistent = persistent;
         fresh->requested_tile_points = o.tile_points;
         fresh->launch0 = plans[0]->launch;
-        fresh->raw.resize(count);
-        for (uint32_t i = 0; i < count; ++i) raw_take(fresh->raw[i], (int)family, plans[i]->d, params[i]);
+        for (uint32_t i = 0; i < count; ++i)
+            if (!raw_append(fresh->raw, (int)family, plans[i]->d, params[i])) break;
         ++g_stats[0];
         if (g_batch.size() >= kMaxContexts) g_batch.erase(g_batch.begin());
         g_batch.push_back(std::move(fresh));

@@ -257,26 +257,32 @@ static bool raw_walk(int family, uint32_t d, const void *params, Fn &&fn) {
     return many(p.a, d) && many(p.u, d);
 }
 
-bool raw_same(const RawParams &raw, int family, uint32_t d, const void *params) {
-    if (raw.family != family) return false;
-    size_t at = 0;
-    const bool all = raw_walk(family, d, params, [&](const void *v, size_t n) {
-        if (raw.bytes.size() - at < n || std::memcmp(&raw.bytes[at], v, n) != 0) return false;
+bool raw_match(const RawParams &raw, size_t &at, int family, uint32_t d, const void *params) {
+    return raw.family == family && raw_walk(family, d, params, [&](const void *v, size_t n) {
+        if (raw.bytes.size() - at < n || std::memcmp(raw.bytes.data() + at, v, n) != 0) return false;
         at += n;
         return true;
     });
-    return all && at == raw.bytes.size();
 }
 
-bool raw_take(RawParams &raw, int family, uint32_t d, const void *params) {
-    raw.family = -1;
-    raw.bytes.clear();
-    if (!raw_walk(family, d, params, [&](const void *v, size_t n) {
-            const auto *b = static_cast<const unsigned char *>(v);
-            raw.bytes.insert(raw.bytes.end(), b, b + n);
-            return true;
-        }))
+bool raw_same(const RawParams &raw, int family, uint32_t d, const void *params) {
+    size_t at = 0;
+    return raw_match(raw, at, family, d, params) && at == raw.bytes.size();
+}
+
+bool raw_append(RawParams &raw, int family, uint32_t d, const void *params) {
+    size_t size = raw.bytes.size();
+    if (!raw_walk(family, d, params, [&](const void *, size_t n) { return size += n, true; })) {
+        raw.family = -1;
         return false;
+    }
+    size_t at = raw.bytes.size();
+    raw.bytes.resize(size);
+    raw_walk(family, d, params, [&](const void *v, size_t n) {
+        std::memcpy(raw.bytes.data() + at, v, n);
+        at += n;
+        return true;
+    });
     raw.family = family;
     return true;
 }
@@ -288,17 +294,19 @@ qmc_status plan_pack(qmc_plan_s *p, int family, const void *params, const Packed
     pk = &p->last_pk;
     if (raw_same(p->last_raw, family, p->d, params)) return QMC_OK;
     p->last_raw.family = -1;
+    p->last_raw.bytes.clear();
     p->last_fn_T = 0;
     const qmc_status st = pack_params(family, p->d, params, p->last_pk);
     if (st) return st;
-    raw_take(p->last_raw, family, p->d, params);
+    raw_append(p->last_raw, family, p->d, params);
     return QMC_OK;
 }
 
 // The table-driven kernels' form of a sector blob (qmc_integrands.hpp):
 // coefficients of degree up to three in their Horner slots (d <= kTabMaxD), the
-// other terms and repeated monomials as coded factor lists.
-std::vector<double> table_blob(const Packed &pk, uint32_t d) {
+// other terms and repeated monomials as coded factor lists.  Formed in `out`;
+// other families' blobs are returned as they are.
+const std::vector<double> &table_blob(const Packed &pk, uint32_t d, std::vector<double> &out) {
     if (pk.key_family != QMC_F_SECTOR && pk.key_family != kFamSectorComplex) return pk.blob;
     const std::vector<double> &b = pk.blob;
     auto word = [&](size_t i) {
@@ -307,7 +315,8 @@ std::vector<double> table_blob(const Packed &pk, uint32_t d) {
         return v;
     };
     const int D = (int)d, size = tab_words(D);
-    std::vector<double> out(kSectorHeader + 2 * (size_t)size, 0.0), lists;
+    out.assign(kSectorHeader + 2 * (size_t)size, 0.0);
+    std::vector<double> lists;
     std::copy(b.begin(), b.begin() + kSectorHeader, out.begin());
     size_t at = kSectorHeader;
     for (int w = 0; w < 2; ++w) {
@@ -502,7 +511,8 @@ qmc_status plan_set_gstep(qmc_plan_s *p, uint32_t S) {
 static qmc_status plan_launch(qmc_plan_s *p, const Packed &pk, LatticeLaunch fn, hipFunction_t jfn, uint32_t T,
                               uint32_t bpc) {
     if (p->m * pk.np > kMaxRows) return fail(QMC_EUNSUPPORTED, "m * parts > %u", kMaxRows);
-    qmc_status st = jfn ? plan_upload_params(p, pk.blob) : plan_upload_params(p, table_blob(pk, p->d));
+    std::vector<double> table;
+    qmc_status st = plan_upload_params(p, jfn ? pk.blob : table_blob(pk, p->d, table));
     if (st) return st;
     const uint32_t tiles = (p->m + T - 1) / T;
     const uint32_t bx = grid_x(p->n, tiles, p->device, bpc);

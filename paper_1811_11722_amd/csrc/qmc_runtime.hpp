@@ -35,7 +35,8 @@ struct Packed {
 };
 
 // The caller's parameters as bytes (every value, no pointer), to recognise the
-// same integrand in a later call by comparing contents.
+// same integrand in a later call by comparing contents; a batch's, one plan's
+// after another.
 struct RawParams {
     int family = -1;  // -1: none
     std::vector<unsigned char> bytes;
@@ -86,8 +87,11 @@ qmc_status fail(qmc_status s, const char *fmt, ...);
 qmc_status hip_fail(hipError_t e, const char *what);
 int device_cu_count(int dev);
 qmc_status pack_params(int family, uint32_t d, const void *params, Packed &pk);
+// whether the bytes from `at` on are these parameters (moves it behind them);
+// whether they are all there is
+bool raw_match(const RawParams &raw, size_t &at, int family, uint32_t d, const void *params);
 bool raw_same(const RawParams &raw, int family, uint32_t d, const void *params);
-bool raw_take(RawParams &raw, int family, uint32_t d, const void *params);
+bool raw_append(RawParams &raw, int family, uint32_t d, const void *params);
 qmc_status plan_pack(qmc_plan_s *p, int family, const void *params, const Packed *&pk);
 qmc_status validate_rule(uint32_t d, uint64_t n, const uint64_t *g, uint32_t m, const double *shifts,
                          qmc_transform &t);
@@ -104,7 +108,7 @@ uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_c
 void gstep_for(const uint32_t *g, uint32_t d, uint32_t n, uint64_t S, uint32_t *out);
 qmc_status ensure_buffer(void **ptr, size_t &cap, size_t bytes, const char *what);
 qmc_status plan_upload_params(qmc_plan_s *p, const std::vector<double> &blob);
-std::vector<double> table_blob(const Packed &pk, uint32_t d);
+const std::vector<double> &table_blob(const Packed &pk, uint32_t d, std::vector<double> &out);
 qmc_status plan_set_gstep(qmc_plan_s *p, uint32_t S);
 qmc_status plan_enqueue(qmc_plan_s *p, const Packed &pk, uint32_t want_T, uint32_t blocks_per_cu);
 qmc_status plan_collect(qmc_plan_s *p, uint32_t np, qmc_result *out, double *per_shift, bool crossing = false);

@@ -100,7 +100,8 @@ extern "C" qmc_status qmc_integrate_static(uint32_t d, uint64_t n, const uint64_
     const uint32_t rows = padded_rows(m);
     const std::vector<double> sh = padded_shifts(std::vector<double>(shifts, shifts + (size_t)m * d), m, d, rows, t);
 
-    const std::vector<double> blob = table_blob(pk, d);
+    std::vector<double> table;
+    const std::vector<double> &blob = table_blob(pk, d, table);
 
     hipStream_t s = (hipStream_t)stream;
     uint32_t *d_g = reinterpret_cast<uint32_t *>(base + kOffG);
