@@ -429,12 +429,19 @@ uint32_t default_tile(int key_family) {
 // 150 us with 32 points per thread, 163 with 8; n = 131071 26.6 us with 8 (two
 // workgroups per CU), 29.3 with 4, 28.5 with 16; n = 16381, m = 16 7.0 us with
 // one, 11.1 with four.
+// Between one and eight workgroups per CU that count is then raised to a whole
+// number per CU: with 2.1 of them on average some CUs have three and the rest
+// wait for those.  Gaussian in d = 12 under Korobov 3, n = 1.1e6, m = 16: 2.1 per
+// CU 164 us, 3 per CU 125, 8 per CU 135; d = 8 sector, m = 28, n = 6e5: 154 (2.0 and
+// a bit), 112 and 137 us.  The nearest whole number instead: 128 and 111 us.
 uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu) {
     const uint64_t cus = (uint64_t)device_cu_count(dev), tiles = std::max<uint32_t>(1, tiles_total);
     auto groups = [n](uint64_t per) { return (n + kBlock * per - 1) / (kBlock * per); };
     const uint64_t cap = std::max({groups(32), std::min(groups(4), 2 * cus / tiles), std::min(groups(1), cus / tiles)});
     const uint64_t bx = std::max<uint64_t>(1, cus * (blocks_per_cu ? blocks_per_cu : 8) / tiles);
-    return (uint32_t)std::max<uint64_t>(std::min(bx, cap), 1);
+    if (bx <= cap) return (uint32_t)bx;
+    const uint64_t whole = (cap * tiles + cus - 1) / cus * cus / tiles;  // at least cap
+    return (uint32_t)std::max<uint64_t>(1, cap * tiles > cus ? std::min(bx, whole) : cap);
 }
 
 void gstep_for(const uint32_t *g, uint32_t d, uint32_t n, uint64_t S, uint32_t *out) {

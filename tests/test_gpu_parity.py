@@ -726,3 +726,27 @@ def test_complex_power_phase_range(Q, p, f):
         _, q = plan.integrate(Q.Params("sector", 1, sector=s))
         plan.close()
         assert np.all(np.abs(q - want) <= 8 * (abs(p) + 4) * 2.0 ** -53 * abs(want)), np.abs(q - want).max()
+
+
+@pytest.mark.parametrize("n,m", [(1099997, 16), (599999, 28), (1048573, 17), (750001, 24), (131071, 16), (16381, 32),
+                                 (4194301, 8)])
+def test_grid_fills_whole_rounds(Q, n, m):
+    """Where a launch has fewer workgroups than asked for, it has a whole number
+    of them per CU (or fewer than one): a fraction leaves some CUs with one more
+    than the others, which then wait.  The estimate does not depend on it
+    (another grid, another summation order: 1e-12 as above)."""
+    import torch
+    d, rng = 4, np.random.default_rng(n)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    plan = Q.Plan(d, n, O.korobov_vector(n, d, 76), rng.random((m, d)), "korobov", 3)
+    p = Q.Params("genz_gaussian", d, a=2 + rng.random(d), u=rng.random(d))
+    _say(f"grid rounds n={n} m={m}")
+    _, q = plan.integrate(p)
+    T, bx, _ = plan.last_launch()
+    tiles = -(-m // T)
+    if bx < 8 * cus // tiles and bx * tiles > cus:
+        assert -bx * tiles % cus < tiles, (bx, tiles, cus)
+    plan.set_launch(T, 2)
+    _, q2 = plan.integrate(p)
+    assert np.all(_rel(q, q2) < TOL)
+    plan.close()
