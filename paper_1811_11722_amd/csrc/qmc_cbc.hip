@@ -365,7 +365,6 @@ struct CbcSelectArgs {
 
 __global__ __launch_bounds__(kBlock) void k_cbc_select(const CbcSelectArgs a) {
     __shared__ double red[3][kBlock / kWave];
-    if (a.state->overflow) return;
     double lo = __builtin_inf(), s1 = 0.0, s2 = 0.0;
     for (uint32_t i = threadIdx.x; i < a.nmin; i += kBlock) lo = __builtin_fmin(lo, a.vmin[i]);
     for (uint32_t i = threadIdx.x; i < kCbcUpd; i += kBlock) {
@@ -604,26 +603,29 @@ uint64_t primitive_root(uint64_t n) {
 constexpr uint64_t kScreenMin = 1000;
 
 // How far apart the errors of a component's candidates lie, to within a
-// factor of a few: the products of its weight and the largest one before it
+// factor of a few: P, the product of its weight and the largest one before it
 // over n^2.  The share of the candidates within the tie width of the best
-// follows it: 0.1 % at 1e-11, 1 % at 1e-12, 20 to 25 % at 2e-13, 73 % at 2e-14,
-// 93 % at 2e-15 (n = 2039, 4099, 16381).  Many ties are too many finalists, and
-// then the component is summed directly after all.  So:
+// follows it, about 1e-14 / P: 0.1 % at 1e-11, 1 % at 1e-12, 20 to 25 % at 2e-13,
+// 73 % at 2e-14, 93 % at 2e-15 (n = 2039, 4099, 16381).  Many ties are too many
+// finalists, and then the component is summed directly after all.  So:
 // - below kTieSure, where no screening pays, a component is not screened if
 //   the direct search is cheap (below kTieDirect points 50 to 300 us a
 //   component, the screening 40 to 60 us); nor with equal errors (0), nor
 //   after a component with a wider spread that had too many ties;
-// - between kTieSure and kTieMaybe it is screened and the host looks at the
-//   outcome before it enqueues the next;
-// - above, every component is enqueued ahead;
+// - below kTieLook times the candidates it is screened and the host looks at
+//   the outcome before it enqueues the next (half of what makes 1024 finalists
+//   by the share above: P is low where several weights are near the largest,
+//   and a look costs 10 us);
+// - above, every component is enqueued ahead; one that has too many finalists
+//   all the same wastes the launches behind it, which return at once;
 // - where all candidates fit the finalists' list (n < 2048), screened and direct
 //   components are not mixed: the direct search of one takes 40 us there, no
 //   more than the buffers and tables of the screening.
-// Trailing zero weights, or weights of 1e-9, at n = 4099, d = 10: 0.80 ms (13 ms
+// Trailing zero weights, or weights of 1e-9, at n = 4099, d = 10: 0.77 ms (13 ms
 // when every component was screened first and all behind it enqueued again
-// after each that had too many ties; 0.82 ms by direct sums alone); at n = 16381
-// 1.00, 13.2 and 1.11 ms.
-constexpr double kTieSure = 5e-13, kTieMaybe = 1e-11;
+// after each that had too many ties; 0.80 ms by direct sums alone); at n = 16381
+// 0.98, 13.2 and 1.10 ms.
+constexpr double kTieSure = 5e-13, kTieLook = 5e-18;
 constexpr uint64_t kTieDirect = 32768;
 
 double cbc_spread(const std::vector<double> &gam, uint32_t c, uint64_t n) {
@@ -835,7 +837,7 @@ extern "C" qmc_status qmc_cbc_search(uint64_t n, uint32_t d, const double *gamma
         const CbcArgs a{(uint32_t)n, jend, 0, ch, inv_n, w, prod, list, fpart};
         // usually one or two finalists; enough workgroups for many where a
         // lattice is a few tiles
-        const uint32_t gy = first ? 1u : std::min(64u, std::max(4u, 512u / (sl * tl)));
+        const uint32_t gy = first ? 1u : std::min(64u, std::max(4u, 256u / (sl * tl)));
         hipLaunchKernelGGL(k_cbc_exact, dim3(sl * tl, gy), dim3(kBlock), 0, nullptr, a, tl, (const CbcState *)state);
         hipLaunchKernelGGL(k_cbc_choose, dim3(1), dim3(1024), 0, nullptr, (const double2 *)fpart, sl * tl, (uint32_t)n,
                            inv_n, w, (const double *)prod, (const uint32_t *)list, state, comp, d_z, d_e2);
@@ -895,7 +897,7 @@ extern "C" qmc_status qmc_cbc_search(uint64_t n, uint32_t d, const double *gamma
                 hipLaunchKernelGGL(k_cbc_select, dim3((N + kBlock - 1) / kBlock), dim3(kBlock), 0, nullptr, sa);
                 exact_step(comp);
                 advance(comp, true);
-                look = N > kCbcFinal && spread(comp) < kTieMaybe;
+                look = N > kCbcFinal && spread(comp) < kTieLook * N;
                 ++comp;
             }
         }
