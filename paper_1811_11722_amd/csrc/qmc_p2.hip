@@ -26,7 +26,8 @@ namespace {
 // Candidates per thread: n = 2^24 - 3, d = 6, 64 candidates take 737 us a search
 // with one, 667 with two, 682 with four and 662 with eight (1016 in the general
 // lattice kernel); n = 2^20 - 3, d = 10: 115, 118, 125 and 141 us, n = 65521,
-// d = 6: 49, 52, 53 and 54 us.
+// d = 6: 49, 52, 53 and 54 us.  A search of one candidate takes one: the second
+// would be a copy.
 constexpr int kP2Cand = 2;
 
 struct P2Args {
@@ -35,7 +36,7 @@ struct P2Args {
     double inv_n;
     double kappa;           // sqrt(2) pi / n
     double c0;              // the factor's constant (p2_constant)
-    const uint32_t *g;      // (groups kP2Cand, D): candidates padded by repeating the last
+    const uint32_t *g;      // (groups C, D): candidates padded by repeating the last
     const uint32_t *gstep;  // (stride g_i) mod n, same layout
     double2 *partials;      // (ncand, nblk)
 };
@@ -52,9 +53,8 @@ double p2_constant(uint64_t n, double kappa) {
     return (double)(1 + pi * pi / (3 * N * N) - mean);
 }
 
-template <int D>
+template <int D, int C>
 __global__ __launch_bounds__(kBlock) void k_p2(const P2Args a) {
-    constexpr int C = kP2Cand;
     const uint32_t c0 = blockIdx.y * C;
     const uint32_t *__restrict__ g = a.g + (size_t)c0 * D;
     const uint32_t *__restrict__ gs = a.gstep + (size_t)c0 * D;
@@ -108,12 +108,13 @@ __global__ __launch_bounds__(kBlock) void k_p2(const P2Args a) {
 }
 
 template <int D>
-hipError_t launch_p2_from(uint32_t d, const P2Args &a, dim3 grid, hipStream_t s) {
+hipError_t launch_p2_from(uint32_t d, uint32_t per_thread, const P2Args &a, dim3 grid, hipStream_t s) {
     if constexpr (D > (int)kMaxDim) {
         return hipErrorInvalidValue;
     } else {
-        if (d != (uint32_t)D) return launch_p2_from<D + 1>(d, a, grid, s);
-        hipLaunchKernelGGL((k_p2<D>), grid, dim3(kBlock), 0, s, a);
+        if (d != (uint32_t)D) return launch_p2_from<D + 1>(d, per_thread, a, grid, s);
+        if (per_thread == 1) hipLaunchKernelGGL((k_p2<D, 1>), grid, dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((k_p2<D, kP2Cand>), grid, dim3(kBlock), 0, s, a);
         return hipGetLastError();
     }
 }
@@ -147,7 +148,8 @@ extern "C" qmc_status qmc_korobov_search(uint64_t n, uint32_t d, const uint64_t 
     bool half = true;
     if ((n & 1) == 0)
         for (uint32_t c = 0; c < ncand; ++c) half = half && (cand[c] % n) % 2 == 1;
-    const uint32_t groups = (ncand + kP2Cand - 1) / kP2Cand, padded = groups * kP2Cand;
+    const uint32_t per_thread = ncand == 1 ? 1 : kP2Cand;
+    const uint32_t groups = (ncand + per_thread - 1) / per_thread, padded = groups * per_thread;
     const uint32_t bx = grid_x((uint32_t)n, groups, dev, 8);
     std::vector<uint32_t> tab(2 * (size_t)padded * d);  // g, then gstep
     uint32_t *g = tab.data(), *gs = g + (size_t)padded * d;
@@ -194,7 +196,7 @@ extern "C" qmc_status qmc_korobov_search(uint64_t n, uint32_t d, const uint64_t 
         t0 = power(factor(0.0));
         if ((n & 1) == 0) t0 += power(factor((double)(n / 2)));  // both self-mirrored terms
     }
-    if ((e = launch_p2_from<1>(d, a, dim3(bx, groups), nullptr)) != hipSuccess) return hip_fail(e, "launch P2 kernel");
+    if ((e = launch_p2_from<1>(d, per_thread, a, dim3(bx, groups), nullptr)) != hipSuccess) return hip_fail(e, "launch P2 kernel");
     FinalizeArgs f{};
     f.partials = a.partials;
     f.nblk = bx;

@@ -637,6 +637,28 @@ def test_korobov_search_edges(Q, n, d, count):
     assert best == every.min() and a == min(int(c) for c, p in zip(cand, every) if p == best)
 
 
+@pytest.mark.parametrize("n,d", [(4093, 1), (65521, 5), (268435399, 12)])
+def test_korobov_search_one_candidate(Q, n, d):
+    """A candidate by itself is computed once, by the sums it has beside
+    another (the same grid), and does not take two candidates' time."""
+    import time
+    _say(f"korobov search one n={n} d={d}")
+    pair = np.array([n // 3, n // 5 + 1], dtype=np.uint64)
+    times = [[], []]
+    for _ in range(5):
+        for k, c in enumerate((pair[:1], pair)):
+            t = time.perf_counter()
+            _, best, every = Q.korobov_search(n, d, c)
+            times[k].append(time.perf_counter() - t)
+            if k == 0:
+                alone = every[0]
+                assert best == alone
+            else:
+                assert every[0] == alone
+    if n > 1 << 27:
+        assert np.median(times[0]) <= 0.75 * np.median(times[1])
+
+
 @pytest.mark.parametrize("tk,alpha", [("none", 0), ("baker", 0), ("korobov", 1), ("korobov", 6)])
 @pytest.mark.parametrize("n", [2, 3, 5, 8])
 @pytest.mark.parametrize("jit", [0, 2])
