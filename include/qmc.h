@@ -557,7 +557,9 @@ qmc_status qmc_lattice_merge(uint32_t m, uint32_t np, const double *q_a, const d
    functions the sector integrand uses against a host reference:
    fn = 0 logarithm (x > 0), 1 exponential: x and y hold count values;
    fn = 2 atan2: x holds count pairs (y_i, x_i), y count angles;
-   fn = 3 sincos (|x| < 2^19): x count values, y count pairs (sin, cos). */
+   fn = 3 sincos (|x| < 2^19): x count values, y count pairs (sin, cos);
+   fn = 4 512 log2 x (x > 0), 5 2^(x/512): x and y hold count values;
+   fn = 6 sin and cos of the sector's phase (|x| < 2^19): as fn = 3. */
 qmc_status qmc_math_eval(int32_t fn, uint64_t count, const double *x, double *y);
 
 /* Release a plan and its device memory (NULL is ignored). */

@@ -969,11 +969,12 @@ qmc_status qmc_deform_select(qmc_plan_t p, const qmc_sector_params *params, doub
 }
 
 qmc_status qmc_math_eval(int32_t fn, uint64_t count, const double *x, double *y) {
-    if (fn < 0 || fn > 3) return fail(QMC_EINVAL, "fn must be 0 (log), 1 (exp), 2 (atan2) or 3 (sincos)");
+    if (fn < 0 || fn > 6)
+        return fail(QMC_EINVAL, "fn must be 0 (log), 1 (exp), 2 (atan2), 3 (sincos), 4 (log512), 5 (exp512) or 6 (phase)");
     if (count && (!x || !y)) return fail(QMC_EINVAL, "null array");
     if (count > (1ull << 28)) return fail(QMC_EINVAL, "count > 2^28");
     if (count == 0) return QMC_OK;
-    const size_t nx = fn == 2 ? 2 * count : count, ny = fn == 3 ? 2 * count : count;
+    const size_t nx = fn == 2 ? 2 * count : count, ny = fn == 3 || fn == 6 ? 2 * count : count;
     DeviceScratch s;
     qmc_status st;
     if ((st = s.alloc(nx * 8)) || (st = s.alloc(ny * 8))) return st;

@@ -107,14 +107,18 @@ std::map<KernelKey, LatticeLaunch> &lattice_registry() {
     return reg;
 }
 
-// device math on an array: fn 0 = qlog, 1 = qexp
+// device math on an array: fn 0 = qlog, 1 = qexp, 2 = qatan2 (of pairs), 3 =
+// qsincos (to pairs), 4 = qlog512, 5 = qexp512, 6 = qphase (to pairs)
 __global__ __launch_bounds__(kBlock) void k_math(int fn, uint64_t count, const double *x, double *y) {
     const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= count) return;
     if (fn == 0) y[i] = qlog(x[i]);
     else if (fn == 1) y[i] = qexp(x[i]);
     else if (fn == 2) y[i] = qatan2(x[2 * i], x[2 * i + 1]);
-    else qsincos(x[i], y[2 * i], y[2 * i + 1]);
+    else if (fn == 3) qsincos(x[i], y[2 * i], y[2 * i + 1]);
+    else if (fn == 4) y[i] = qlog512(x[i]);
+    else if (fn == 5) y[i] = qexp512(x[i]);
+    else qphase(x[i], y[2 * i], y[2 * i + 1]);
 }
 
 hipError_t launch_math(int fn, uint64_t count, const double *x, double *y, hipStream_t s) {

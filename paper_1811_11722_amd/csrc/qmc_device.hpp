@@ -110,9 +110,11 @@ __device__ __forceinline__ double divide(double a, double b) {
 }
 
 // ------------------------------------------------- FP64 exp and log
-// gfx950 has no FP64 exponential or logarithm instruction.  These two are
-// written for the sector integrand's U^a F^b = exp(a ln U + b ln F): finite
-// arguments, no errno or special-case branches.
+// gfx950 has no FP64 exponential or logarithm instruction.  These two take
+// finite arguments and have no errno or special-case branches.  qexp serves the
+// Genz functions; both form the powers U^a F^b = exp(a ln U + b ln F) of the
+// training samples (sector_sample), whose bits are kept; the estimate's sectors
+// take qlog512 and qexp512 below.
 
 // The tables of qlog and qexp in one 8 KB array (written by
 // make_math_tables.py), so that one base address serves both: entries 2j and
@@ -1481,12 +1483,14 @@ __device__ __forceinline__ const double *pow_tab(uint32_t byte) {
 // 2^(y/512).  Against exp(p ln x) the logarithm's exponent joins by one FMA
 // instead of two and an add, its series is one Horner chain onto the table
 // value, and the exponential's reduction is an exact subtraction instead of a
-// multiply and two FMAs: 4 to 5 instructions less per power.  Errors are
-// those of qlog and qexp: half an ulp of the logarithm on the scale of the
-// larger of it and 512 (ln 2), carried into the power by p.
+// multiply and two FMAs: 4 to 5 instructions less per power.  The logarithm's
+// error, carried into the power by p ln2 / 512, is of the size of qlog's: a few
+// 2^-53 on the scale of the larger of it and 512 (ln 2).
 
 // 512 log2 x for x > 0 (NaN otherwise), as qlog: x = m 2^e, r = m ic_j - 1,
-// 512 e + (t_j + 512 log2(1 + r)) with the series to r^5.
+// 512 e + (t_j + 512 log2(1 + r)) with the series to r^5.  Half an ulp of the
+// result plus at most 2.3 2^-45: half an ulp of 512 for the table entry, as much
+// for the inner sum, a quarter of it for the series' end.
 __device__ __forceinline__ double qlog512(double x) {
     constexpr double c = 738.6598609351493;  // 512 log2(e)
     const double m = __builtin_amdgcn_frexp_mant(x);
@@ -1505,7 +1509,8 @@ __device__ __forceinline__ double qlog512(double x) {
 }
 
 // 2^(y/512): k = rint(y), f = y - k exactly, 2^(k >> 9) 2^((k & 511)/512)
-// 2^(f/512) with the last factor's series to f^4 (|f| ln2/512 <= 6.8e-4).
+// 2^(f/512) with the last factor's series to f^4 (|f| ln2/512 <= 6.8e-4): half an
+// ulp for the table entry and half of one for the product.
 __device__ __forceinline__ double qexp512(double y) {
     constexpr double l = 0.0013538030870311431;  // ln2 / 512
     const double k = __builtin_rint(y);
@@ -1596,7 +1601,8 @@ __device__ __forceinline__ void qsincos(double x, double &sn, double &cs) {
 // pi/256 (the split of pi/2 above, scaled), the table's angle by k mod 256 and
 // a rotation by r, sin r to r^5 and cos r to r^6 (truncation below 1e-17): 21
 // instructions against the 35 of qsincos, which reduces to pi/4 and selects
-// quadrants.
+// quadrants.  Absolute error 1.2 2^-53: half an ulp of 1 for the table entry and
+// for the sum.
 __device__ __forceinline__ void qphase(double x, double &sn, double &cs) {
     constexpr double k128Pi = 64.0 * 0x1.45f306dc9c883p-1;
     const double k = __builtin_rint(x * k128Pi);

@@ -406,14 +406,16 @@ class Plan:
 
 
 def math_eval(fn: str, x, x2=None) -> np.ndarray:
-    """Device math on arrays: 'log', 'exp', 'atan2' (math_eval('atan2', y, x))
-    or 'sincos' (returns an (n, 2) array of sin, cos)."""
-    code = {"log": 0, "exp": 1, "atan2": 2, "sincos": 3}[fn]
+    """Device math on arrays: 'log', 'exp', 'atan2' (math_eval('atan2', y, x)),
+    'sincos' (returns an (n, 2) array of sin, cos), and the sector's power
+    functions 'log512' (512 log2 x), 'exp512' (2^(x/512)) and 'phase' (as
+    'sincos')."""
+    code = {"log": 0, "exp": 1, "atan2": 2, "sincos": 3, "log512": 4, "exp512": 5, "phase": 6}[fn]
     x = _arr(x, np.float64)
     n = x.size
     if code == 2:
         x = _arr(np.stack([x, _arr(x2, np.float64)], axis=-1), np.float64)
-    y = np.zeros((n, 2) if code == 3 else n)
+    y = np.zeros((n, 2) if code in (3, 6) else n)
     check(lib().qmc_math_eval(code, n, _p(x), _p(y)), "qmc_math_eval")
     return y
 

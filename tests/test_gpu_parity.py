@@ -108,6 +108,51 @@ def test_device_atan2_sincos(Q):
         assert np.all(err <= bound), (col, err.max())
 
 
+def test_device_powers_and_phase(Q):
+    """qlog512, qexp512 and qphase (the sectors' powers and phases) against long
+    double on the arguments of the tests above and their edges: subnormals,
+    the largest double, values beside 1, 0, negative, infinite and NaN; overflow,
+    underflow into the subnormals and out; phases up to 2^19.  The bounds are
+    those stated beside the functions, plus 2^-60 for the reference."""
+    rng = np.random.default_rng(7)
+    x = np.concatenate([10.0 ** rng.uniform(-300, 300, 200000), rng.uniform(0.5, 2.0, 200000),
+                        1.0 + rng.uniform(-1e-6, 1e-6, 50000), 2.0 ** -1074 * rng.integers(1, 1 << 52, 50000),
+                        [1.0, 2.0, 0.5, 1e-308, 5e-324, 2.2250738585072014e-308, 1.7976931348623157e308,
+                         np.nextafter(1.0, 2), np.nextafter(1.0, 0), np.nextafter(0.5, 0), np.nextafter(2.0, 0)]])
+    _say("device log512")
+    y = Q.math_eval("log512", x)
+    ref = 512 * np.log2(x.astype(np.longdouble))
+    err = np.abs((y - ref).astype(np.float64))
+    bound = 2.3 * 2.0 ** -45 + 0.5 * np.spacing(np.abs(ref.astype(np.float64))) + np.abs(ref.astype(np.float64)) * 2.0 ** -60
+    print("  largest error / bound", (err / bound).max())
+    assert np.all(err <= bound)
+    assert np.all(np.isnan(Q.math_eval("log512", np.array([0.0, -0.0, -1.0, -np.inf, np.inf, np.nan]))))
+    t = np.concatenate([rng.uniform(-512 * 1020, 512 * 1020, 200000), rng.uniform(-512, 512, 200000),
+                        rng.uniform(-512 * 1075, -512 * 1021, 50000), rng.integers(-4000, 4000, 2000) + 0.5,
+                        [0.0, -0.0, 0.5, -0.5, 512.0, -512 * 1022.0, -512 * 1074.0, np.nextafter(512 * 1024.0, 0)]])
+    _say("device exp512")
+    y = Q.math_eval("exp512", t)
+    ref = np.exp2(t.astype(np.longdouble) / 512)
+    err = np.abs(y - ref)
+    bound = 2.05 * 2.0 ** -53 * ref + 2.0 ** -60 * ref + np.where(ref < 2.3e-308, np.longdouble(2) ** -1075, np.longdouble(0))
+    print("  largest error / bound", float((err / bound).max()))
+    assert np.all(err <= bound)
+    big = np.array([512 * 1024.0, 1e7, 1e15, 1e300])
+    assert np.all(Q.math_eval("exp512", big) == np.inf) and np.all(Q.math_eval("exp512", -1.1 * big) == 0.0)
+    assert np.isnan(Q.math_eval("exp512", np.array([np.nan]))[0])
+    t = np.concatenate([rng.uniform(-4.5, 4.5, 200000), rng.uniform(-1e5, 1e5, 100000),
+                        rng.uniform(-2.0 ** 19, 2.0 ** 19, 100000), np.pi / 128 * rng.integers(-4000, 4000, 20000),
+                        np.pi / 256 * (2 * rng.integers(-4000, 4000, 20000) + 1),
+                        [0.0, -0.0, np.pi / 4, np.pi / 2, -np.pi, 1e-300, 5e-324, np.nextafter(2.0 ** 19, 0)]])
+    _say("device phase")
+    sc = Q.math_eval("phase", t)
+    tl = t.astype(np.longdouble)
+    for col, ref in ((0, np.sin(tl)), (1, np.cos(tl))):
+        err = np.abs((sc[:, col] - ref).astype(np.float64))
+        print("  largest error / 2^-53", err.max() * 2.0 ** 53)
+        assert np.all(err <= 1.2 * 2.0 ** -53 + 2.0 ** -60), col
+
+
 def test_korobov_constant_error_decay(Q):
     """Sec. 2, Fig. 3: integrating 1 with the Korobov weight-3 transform in
     d = 6, the reported error falls far faster than 1/n, and the per-shift
