@@ -127,6 +127,14 @@ hipError_t launch_math(int fn, uint64_t count, const double *x, double *y, hipSt
     return hipGetLastError();
 }
 
+// The one last node of a captured graph with parallel branches.
+__global__ void k_join() {}
+
+hipError_t launch_join(hipStream_t s) {
+    hipLaunchKernelGGL(k_join, dim3(1), dim3(1), 0, s);
+    return hipGetLastError();
+}
+
 // Clears a small counter array (used inside captured graphs, where a memset
 // node is avoided).
 __global__ void k_zero_u32(uint32_t *p, uint32_t count) {

@@ -74,6 +74,7 @@ hipError_t launch_finalize(const FinalizeArgs &a, uint32_t ninst, hipStream_t s)
 hipError_t launch_dump(const DumpArgs &a, uint32_t blocks, hipStream_t s);
 hipError_t launch_math(int fn, uint64_t count, const double *x, double *y, hipStream_t s);
 hipError_t launch_zero_u32(uint32_t *p, uint32_t count, hipStream_t s);
+hipError_t launch_join(hipStream_t s);
 hipError_t launch_finalize_batch(const FinalizeBatchArgs &a, uint32_t count, hipStream_t s);
 
 }  // namespace qmc

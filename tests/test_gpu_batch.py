@@ -345,3 +345,39 @@ def test_jit_code_object_store(Q, tmp_path):
         assert sorted(files) == sorted(f for f in os.listdir(tmp_path) if f.endswith(".co"))
     finally:
         del os.environ["QMC_JIT_CACHE"]
+
+
+@pytest.mark.parametrize("count", [1, 2, 3, 4, 5, 9])
+def test_specialised_graph_of_few_plans(Q, count):
+    """Fewer plans than the graph's branches, as many, more: replays with
+    changed coefficients, with eager estimates of the same plans in between,
+    give the eager results bit for bit, and a replay takes no more than a
+    third longer than the eager launches (best of 31)."""
+    import time
+    n, m = 16381, 16
+    tabs = [synth.sector_tables(50 + i % 4, 2 + i % 4, 8, 20) for i in range(count)]
+    plans = [Q.Plan(t.d, n, O.korobov_vector(n, t.d, 76), synth.shifts(i, m, t.d), "baker")
+             for i, t in enumerate(tabs)]
+    params = [Q.Params("sector", t.d, sector=t) for t in tabs]
+    _say(f"specialised graph of {count}")
+
+    def call(graph):
+        t = time.perf_counter()
+        rs = Q.integrate_batch(plans, params, schedule="specialised", use_graph=graph)
+        return time.perf_counter() - t, [(r.mean_re, r.err_re) for r in rs]
+
+    for k in range(4):
+        for i, p in enumerate(params):
+            p.keep[0][0] *= 1.0 + 0.01 * (k + i)
+        got = call(True)[1]
+        assert got == call(False)[1]
+        single = [plan.integrate(p)[0] for plan, p in zip(plans, params)]
+        assert got == [(r.mean_re, r.err_re) for r in single]
+        assert got == call(True)[1]
+    times = [[call(g)[0] for _ in range(31)] for g in (True, False)]
+    graph, eager = (min(t) for t in times)
+    print(f"  graph {1e6 * graph:.0f} us, eager {1e6 * eager:.0f} us")
+    if count >= 4:
+        assert graph <= 4 / 3 * eager
+    for p in plans:
+        p.close()
