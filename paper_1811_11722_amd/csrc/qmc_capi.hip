@@ -434,10 +434,12 @@ uint32_t default_tile(int key_family) {
 // wait for those.  Gaussian in d = 12 under Korobov 3, n = 1.1e6, m = 16: 2.1 per
 // CU 164 us, 3 per CU 125, 8 per CU 135; d = 8 sector, m = 28, n = 6e5: 154 (2.0 and
 // a bit), 112 and 137 us.  The nearest whole number instead: 128 and 111 us.
-uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu) {
+// min_points: 32, or what the caller's kernel needs (the control-variate residual,
+// see there).
+uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu, uint32_t min_points) {
     const uint64_t cus = (uint64_t)device_cu_count(dev), tiles = std::max<uint32_t>(1, tiles_total);
     auto groups = [n](uint64_t per) { return (n + kBlock * per - 1) / (kBlock * per); };
-    const uint64_t cap = std::max({groups(32), std::min(groups(4), 2 * cus / tiles), std::min(groups(1), cus / tiles)});
+    const uint64_t cap = std::max({groups(min_points), std::min(groups(4), 2 * cus / tiles), std::min(groups(1), cus / tiles)});
     const uint64_t bx = std::max<uint64_t>(1, cus * (blocks_per_cu ? blocks_per_cu : 8) / tiles);
     if (bx <= cap) return (uint32_t)bx;
     const uint64_t whole = (cap * tiles + cus - 1) / cus * cus / tiles;  // at least cap
@@ -516,13 +518,13 @@ qmc_status plan_set_gstep(qmc_plan_s *p, uint32_t S) {
 // Enqueue the lattice kernel (a registry launcher or a specialised module
 // function) and the finalize kernel of one estimate.
 static qmc_status plan_launch(qmc_plan_s *p, const Packed &pk, LatticeLaunch fn, hipFunction_t jfn, uint32_t T,
-                              uint32_t bpc) {
+                              uint32_t bpc, uint32_t min_points = 32) {
     if (p->m * pk.np > kMaxRows) return fail(QMC_EUNSUPPORTED, "m * parts > %u", kMaxRows);
     std::vector<double> table;
     qmc_status st = plan_upload_params(p, jfn ? pk.blob : table_blob(pk, p->d, table));
     if (st) return st;
     const uint32_t tiles = (p->m + T - 1) / T;
-    const uint32_t bx = grid_x(p->n, tiles, p->device, bpc);
+    const uint32_t bx = grid_x(p->n, tiles, p->device, bpc, min_points);
     if ((st = plan_set_gstep(p, bx * kBlock))) return st;
     const size_t pbytes = (size_t)p->m * pk.np * bx * sizeof(double2);
     if ((st = ensure_buffer((void **)&p->d_partials, p->partials_cap, pbytes, "partials"))) return st;
@@ -563,8 +565,8 @@ static qmc_status plan_launch(qmc_plan_s *p, const Packed &pk, LatticeLaunch fn,
     return QMC_OK;
 }
 
-qmc_status plan_enqueue_fn(qmc_plan_s *p, const Packed &pk, hipFunction_t jfn, uint32_t T) {
-    return plan_launch(p, pk, nullptr, jfn, T, p->launch.blocks_per_cu);
+qmc_status plan_enqueue_fn(qmc_plan_s *p, const Packed &pk, hipFunction_t jfn, uint32_t T, uint32_t min_points) {
+    return plan_launch(p, pk, nullptr, jfn, T, p->launch.blocks_per_cu, min_points);
 }
 
 // Shifts per thread of the specialised kernels: four for real sectors of up to

@@ -2354,7 +2354,12 @@ qmc_status qmc_integrate_cv(qmc_plan_t p, qmc_family family, const void *params,
     Packed cv = pk;
     cv.np = 2 * nm;
     cv.key_family = -1;  // not in the kernel registry
-    if ((st = plan_enqueue_fn(p, cv, fn, 1))) return st;
+    // Down to 4 points per thread: this kernel's waves wait on chains of matrix
+    // instructions, and two of them on a CU leave it idle.  R = 16, K = 8, d = 6,
+    // n = 1048573, m = 4: 8 workgroups per CU 199 us, the 2 that 32 points per
+    // thread leave 213; R = 64, K = 12, d = 10 complex, n = 131071, m = 12: 1264 and
+    // 1321 us.
+    if ((st = plan_enqueue_fn(p, cv, fn, 1, 4))) return st;
     qmc_result first;
     std::vector<double> q((size_t)cv.np * p->m);
     st = plan_collect(p, cv.np, &first, q.data());

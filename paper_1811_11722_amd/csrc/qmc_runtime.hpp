@@ -104,7 +104,7 @@ double transform_scale(const qmc_transform &t, uint32_t d);
 LatticeLaunch find_kernel(int key_family, const qmc_transform &t, uint32_t d, uint32_t want_T, uint32_t &T_out);
 uint32_t default_tile(int key_family);
 uint32_t jit_tile(const Packed &pk, uint32_t d);
-uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu);
+uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu, uint32_t min_points = 32);
 void gstep_for(const uint32_t *g, uint32_t d, uint32_t n, uint64_t S, uint32_t *out);
 qmc_status ensure_buffer(void **ptr, size_t &cap, size_t bytes, const char *what);
 qmc_status plan_upload_params(qmc_plan_s *p, const std::vector<double> &blob);
@@ -128,7 +128,7 @@ hipFunction_t jit_cv_kernel(const std::vector<double> &blob, size_t cv_off, uint
 hipFunction_t jit_sample_kernel(const std::vector<double> &blob, uint32_t d, const qmc_transform &tr, bool cplx, int dev,
                                 std::string &err);
 hipError_t jit_launch_sample(hipFunction_t fn, const CvSampleArgs &a, uint32_t blocks, hipStream_t s);
-qmc_status plan_enqueue_fn(qmc_plan_s *p, const Packed &pk, hipFunction_t jfn, uint32_t T);
+qmc_status plan_enqueue_fn(qmc_plan_s *p, const Packed &pk, hipFunction_t jfn, uint32_t T, uint32_t min_points);
 std::string tune_key(const qmc_plan_s *p, const Packed &pk, bool jit);
 bool tune_lookup(const qmc_plan_s *p, const Packed &pk, bool jit, qmc_launch &out);
 

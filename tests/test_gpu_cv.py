@@ -239,3 +239,20 @@ def test_cv_complex_training(Q):
     er = O.estimate(n, g, sh, O.Params("sector", d, sector=tab, cv=(W, c)), "baker", threads=THREADS)
     er_q = er.q_re + 1j * er.q_im
     assert np.all(np.abs(qr - er_q) <= 1e-12 * np.maximum(np.abs(qp), np.abs(er_q)))
+
+
+def test_residual_grid_keeps_waves(Q):
+    """The residual kernel takes as few as four points per thread, so that a CU
+    has waves to change between (the estimate's other kernels stop at 32):
+    eight workgroups per CU where the lattice allows it."""
+    import torch
+    d, n, m, R, K = 3, 1048573, 4, 8, 8
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(6)
+    plan = Q.Plan(d, n, O.korobov_vector(n, d, 76), synth.shifts(6, m, d), "korobov", 2)
+    print("[gpu-case] residual grid", flush=True)
+    plan.integrate_cv(Q.Params("sector", d, sector=synth.sector_tables(6, d, 5, 9)), 0.1 * rng.standard_normal((R, d, K)),
+                      rng.random(R))
+    T, bx, _ = plan.last_launch()
+    assert T == 1 and bx * m == 8 * cus
+    plan.close()
