@@ -72,6 +72,11 @@ struct FamCvResidual {
     static constexpr int NM = Base::NP;  // one model per component
     static constexpr int NP = 2 * NM;
     static constexpr bool kWaveUniform = true;  // the whole wave runs the matrix instructions
+    // Large models keep the point loop's registers for their fragments: the shifts
+    // staged in LDS against scalars and 1/n in a vector register, n = 1048573,
+    // m = 32: R = 64, K = 12, d = 8 9.30 against 9.43 ms, d = 10 complex 23.9 and
+    // 24.1, R = 32, K = 16, d = 5 3.26 and 3.27; R = 32, K = 12, d = 8 3.94 and 3.92.
+    static constexpr bool kShiftsInLds = R * K > 384;
     static constexpr int RB = (R + 15) / 16, KS = (K + 3) / 4;
 
     // g of the lane's own point for the model whose fragments start at w
