@@ -45,8 +45,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // staged in LDS once per workgroup and the coordinates of a point all
 // loaded before the first is used.  Up to 32 ranks a coordinate and its
 // weights are loaded one dimension ahead (the next round's first one at the
-// end of a round) and the loop has no other branch: three waves per SIMD
-// instead of two, and a round waits on memory no more.  Bound by the FP64
+// end of a round) and the loop has no other branch, so that a round waits on
+// memory no more (three waves per SIMD or two make no difference then).  Bound by the FP64
 // units (the products, 2 R K per point and dimension, and the recurrences);
 // 1048573 points, d = 8, R = 32, K = 12: 178 us before, 134 us now
 // (5.6 GFLOP of products: 42 TFLOP/s, and 269 MB of rho).  The product over
@@ -1914,8 +1914,11 @@ struct CvTrainer {
 
     void features(uint32_t i, hipStream_t st) {
         const CvRhoArgs ra{n, d, i, z, sw, ws, rho, phi, zi};
-        // three workgroups per CU up to 32 ranks (k_cv_rho's registers)
-        fn.rho(ra, std::min<uint32_t>(rblocks, 768), st);
+        // up to 32 ranks three workgroups per CU, as many as k_cv_rho's registers
+        // allow; 64 ranks run one wave per SIMD at a time, and four workgroups
+        // per CU end more evenly than three (1048573 points, d = 10, K = 12: 415 us
+        // against 431)
+        fn.rho(ra, std::min<uint32_t>(rblocks, R <= 32 ? 768 : 1024), st);
     }
 
     // A0 = sum_j a~_j a~_j^T (BF16 MFMA, FP32 accumulation per split, FP64 over splits)
