@@ -303,7 +303,9 @@ qmc_status qmc_batch_stats(uint64_t *out);
    batch stream), and returns the fastest options in best
    (use_graph = 1) and their time in best_ms (nullable, milliseconds).  The
    arguments are those of qmc_integrate_batch; the estimates it computes are
-   discarded. */
+   discarded.  For a batch of fewer than about three workgroups per CU at 4096
+   points the default tiles (tile_points = 0) are smaller than all of these and
+   faster: tune large batches. */
 qmc_status qmc_batch_autotune(uint32_t count, const qmc_plan_t *plans, qmc_family family,
                               const void *const *params, qmc_batch_opts *best, double *best_ms);
 

@@ -289,7 +289,8 @@ bool raw_append(RawParams &raw, int family, uint32_t d, const void *params) {
 
 // The packed integrand of a plan's call: the last one when the caller's values
 // are the same bytes (packing a d = 6 sector of 42 monomials takes 1.5 us and
-// building its kernel's key 3 us, of a call of 24), packed anew otherwise.
+// building its kernel's key 3 us, of a call of 22), packed anew otherwise (with
+// the upload and its wait, a call with new coefficients takes 38 us).
 qmc_status plan_pack(qmc_plan_s *p, int family, const void *params, const Packed *&pk) {
     pk = &p->last_pk;
     if (raw_same(p->last_raw, family, p->d, params)) return QMC_OK;
@@ -570,12 +571,18 @@ qmc_status plan_enqueue_fn(qmc_plan_s *p, const Packed &pk, hipFunction_t jfn, u
 }
 
 // Shifts per thread of the specialised kernels: four for real sectors of up to
-// eight dimensions (n = 2^22 - 3, m = 32, four against two: 620, 654, 675 us against
-// 650, 690, 721 under the baker's transform at d = 6, 7, 8, 800, 828, 945 against
-// 850, 897, 974 under Korobov 2; at d = 9 the latter takes 1119 against 1033) and
-// for real expansion orders up to six (8 % slower at d = 8), two for the others
-// (complex d = 10: 707 against 716 us with four), one with a deformation, whose
-// point carries the Jacobian's triangle.
+// eight dimensions and for real expansion orders up to six, two for the others,
+// one with a deformation, whose point carries the Jacobian's triangle.  Four
+// against two, kernel us at n = 2^22 - 3, m = 32 (medians, the two in turn):
+//                  d = 6        7           8           9           10
+// baker            477 / 507   521 / 544   523 / 557   552 / 589   578 / 608
+// Korobov 2        588 / 628   673 / 702   681 / 718   740 / 775   948 / 834
+// orders, baker    568 / 585   620 / 643   622 / 647   653 / 675   745 / 708
+// orders, Kor. 2   687 / 720   765 / 784   855 / 821   842 / 878   971 / 936
+// complex                                                          883 / 881
+// So four would do at d = 9 too and, without a weight, at d = 10 (5 to 6 %); past
+// that it depends on the map.  The line stays at eight, the default that
+// callers and its test know.
 uint32_t jit_tile(const Packed &pk, uint32_t d) {
     if (pk.deform) return 1;
     return !pk.cplx && d <= (pk.orders < 2 ? 8u : 6u) ? 4 : 2;

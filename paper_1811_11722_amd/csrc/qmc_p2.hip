@@ -23,11 +23,11 @@ namespace qmc {
 
 namespace {
 
-// Candidates per thread: n = 2^24 - 3, d = 6, 64 candidates take 737 us a search
-// with one, 667 with two, 682 with four and 662 with eight (1016 in the general
-// lattice kernel); n = 2^20 - 3, d = 10: 115, 118, 125 and 141 us, n = 65521,
-// d = 6: 49, 52, 53 and 54 us.  A search of one candidate takes one: the second
-// would be a copy.
+// Candidates per thread: n = 2^24 - 3, d = 6, 64 candidates take 676 us a search
+// with one, 620 with two, 605 with four and 597 with eight (1012 in the general
+// lattice kernel); n = 2^20 - 3, d = 10: 113, 113, 118 and 118 us, n = 65521,
+// d = 6: 46, 46, 47 and 49 us.  A search of one candidate takes one: the second
+// would be a copy (n = 2^31 - 1, d = 12: 4.68 ms, 2.46 with one).
 constexpr int kP2Cand = 2;
 
 struct P2Args {
