@@ -161,7 +161,8 @@ qmc_status build_uniform(BatchCtx &c, uint32_t count, const qmc_plan_t *plans, c
     c.T = T;
     c.ltiles = (m + T - 1) / T;
     if ((uint64_t)count * c.ltiles > 65535) return fail(QMC_EUNSUPPORTED, "too many instances for one launch");
-    c.lbx = grid_x(n, count * c.ltiles, c.device, p0->launch.blocks_per_cu ? p0->launch.blocks_per_cu : 8);
+    const uint32_t bpc = p0->launch.blocks_per_cu;
+    c.lbx = grid_x(n, count * c.ltiles, c.device, bpc ? bpc : 8, bpc ? 4 : 32);
     size_t pstride = 0;
     std::vector<std::vector<double>> tables(count);
     std::vector<const std::vector<double> *> blobs(count);
@@ -506,7 +507,8 @@ static qmc_status spec_prepare(qmc_plan_s *p, const Packed &pk, SpecPlan &sp) {
     if (!sp.fn) return fail(QMC_EUNSUPPORTED, "specialised sector kernel: %s", err.c_str());
     if (p->m * pk.np > kMaxRows) return fail(QMC_EUNSUPPORTED, "m * parts > %u", kMaxRows);
     sp.tiles = (p->m + sp.T - 1) / sp.T;
-    sp.bx = grid_x(p->n, sp.tiles, p->device, p->launch.blocks_per_cu ? p->launch.blocks_per_cu : 16);
+    const uint32_t bpc = p->launch.blocks_per_cu;
+    sp.bx = grid_x(p->n, sp.tiles, p->device, bpc ? bpc : 16, bpc ? 4 : 32);
     qmc_status st = plan_upload_params(p, pk.blob);
     if (!st) st = plan_set_gstep(p, sp.bx * kBlock);
     if (!st)

@@ -435,8 +435,9 @@ uint32_t default_tile(int key_family) {
 // wait for those.  Gaussian in d = 12 under Korobov 3, n = 1.1e6, m = 16: 2.1 per
 // CU 164 us, 3 per CU 125, 8 per CU 135; d = 8 sector, m = 28, n = 6e5: 154 (2.0 and
 // a bit), 112 and 137 us.  The nearest whole number instead: 128 and 111 us.
-// min_points: 32, or what the caller's kernel needs (the control-variate residual,
-// see there).
+// min_points: 32 by default; 4 where the caller asked for a number of workgroups
+// per CU (a plan's launch configuration, the autotuner) and for kernels that need
+// more waves (the control-variate residual, see there).
 uint32_t grid_x(uint32_t n, uint32_t tiles_total, int dev, uint32_t blocks_per_cu, uint32_t min_points) {
     const uint64_t cus = (uint64_t)device_cu_count(dev), tiles = std::max<uint32_t>(1, tiles_total);
     auto groups = [n](uint64_t per) { return (n + kBlock * per - 1) / (kBlock * per); };
@@ -519,7 +520,7 @@ qmc_status plan_set_gstep(qmc_plan_s *p, uint32_t S) {
 // Enqueue the lattice kernel (a registry launcher or a specialised module
 // function) and the finalize kernel of one estimate.
 static qmc_status plan_launch(qmc_plan_s *p, const Packed &pk, LatticeLaunch fn, hipFunction_t jfn, uint32_t T,
-                              uint32_t bpc, uint32_t min_points = 32) {
+                              uint32_t bpc, uint32_t min_points) {
     if (p->m * pk.np > kMaxRows) return fail(QMC_EUNSUPPORTED, "m * parts > %u", kMaxRows);
     std::vector<double> table;
     qmc_status st = plan_upload_params(p, jfn ? pk.blob : table_blob(pk, p->d, table));
@@ -614,12 +615,14 @@ qmc_status plan_enqueue(qmc_plan_s *p, const Packed &pk, uint32_t want_T, uint32
         if (!fn)
             return fail(QMC_EUNSUPPORTED, "no kernel for family %d, transform %d/%d, d = %u", pk.key_family,
                         p->tr.kind, p->tr.alpha, p->d);
-    } else if (bpc == 0) {
+    }
+    const uint32_t min_points = bpc ? 4 : 32;  // a number asked for is kept
+    if (jfn && bpc == 0) {
         // the specialised sector kernels hold few enough registers for four
         // waves per SIMD; 16 workgroups per CU fill whole residency rounds
         bpc = 16;
     }
-    return plan_launch(p, pk, fn, jfn, T, bpc);
+    return plan_launch(p, pk, fn, jfn, T, bpc, min_points);
 }
 
 qmc_status plan_collect(qmc_plan_s *p, uint32_t np, qmc_result *out, double *per_shift, bool crossing) {
@@ -911,7 +914,8 @@ qmc_status qmc_integrate_sum(qmc_plan_t p, uint32_t count, const qmc_sector_para
     std::string err;
     hipFunction_t jfn = jit_sum_kernel(sum.blob, offs, p->d, p->tr, T, sum.cplx, p->device, err);
     if (!jfn) return fail(QMC_EUNSUPPORTED, "specialised sum kernel: %s", err.c_str());
-    qmc_status st = plan_launch(p, sum, nullptr, jfn, T, p->launch.blocks_per_cu ? p->launch.blocks_per_cu : 16);
+    const uint32_t bpc = p->launch.blocks_per_cu;
+    qmc_status st = plan_launch(p, sum, nullptr, jfn, T, bpc ? bpc : 16, bpc ? 4 : 32);
     if (st) return st;
     return plan_collect(p, sum.np, out, per_shift);
 }

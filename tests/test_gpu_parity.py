@@ -817,3 +817,21 @@ def test_grid_fills_whole_rounds(Q, n, m):
     _, q2 = plan.integrate(p)
     assert np.all(_rel(q, q2) < TOL)
     plan.close()
+
+
+@pytest.mark.parametrize("jit", [0, 1])
+@pytest.mark.parametrize("n,m,bpc", [(1048573, 17, 8), (1048573, 4, 8), (262139, 7, 4), (16777213, 32, 32), (16381, 32, 16)])
+def test_launch_configuration_is_kept(Q, n, m, bpc, jit):
+    """A number of workgroups per CU asked for is launched, down to four points
+    per thread (the default's limit of 32 is not meant for it)."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    plan = Q.Plan(3, n, O.korobov_vector(n, 3, 76), synth.shifts(8, m, 3), "baker")
+    plan.set_jit(jit)
+    plan.set_launch(4, bpc)
+    _say(f"launch configuration n={n} m={m} bpc={bpc} jit={jit}")
+    plan.integrate(Q.Params("sector", 3, sector=synth.sector_tables(8, 3, 5, 9)))
+    T, bx, _ = plan.last_launch()
+    tiles, most = -(-m // T), -(-n // (256 * 4))
+    assert T == 4 and (bx == bpc * cus // tiles if bpc * cus // tiles <= most else bx >= most)
+    plan.close()
