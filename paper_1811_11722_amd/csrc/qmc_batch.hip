@@ -479,17 +479,6 @@ bool same_raw(const BatchCtx &c, uint32_t count, const qmc_plan_t *plans, int fa
 
 }  // namespace
 
-void plan_release_extra(qmc_plan_s *p) {
-    std::lock_guard<std::mutex> lock(g_batch_mu);
-    g_batch.erase(std::remove_if(g_batch.begin(), g_batch.end(),
-                                 [p](const std::unique_ptr<BatchCtx> &c) {
-                                     return std::find(c->plans.begin(), c->plans.end(), p) != c->plans.end();
-                                 }),
-                  g_batch.end());
-    delete p->extra;
-    p->extra = nullptr;
-}
-
 // One launch per plan of its run-time specialised sector kernel (each plan's
 // own stream and buffers), then one synchronisation per plan's stream.
 // Launch shape of one plan's specialised sector kernel, as plan_enqueue
@@ -574,6 +563,23 @@ struct SpecCtx {
     }
 };
 std::vector<std::unique_ptr<SpecCtx>> g_spec;
+
+// Forgets every context and captured graph that holds the plan: another plan at
+// its address, with buffers at theirs, is not the same plan.
+void plan_release_extra(qmc_plan_s *p) {
+    std::lock_guard<std::mutex> lock(g_batch_mu);
+    auto drop = [p](auto &all) {
+        all.erase(std::remove_if(all.begin(), all.end(),
+                                 [p](const auto &c) {
+                                     return std::find(c->plans.begin(), c->plans.end(), p) != c->plans.end();
+                                 }),
+                  all.end());
+    };
+    drop(g_batch);
+    drop(g_spec);
+    delete p->extra;
+    p->extra = nullptr;
+}
 
 static std::vector<const void *> spec_buffers(qmc_plan_s *p) {
     return {p->d_params, p->d_partials, p->d_gstep, p->d_g, p->d_shifts, p->h_out};

@@ -775,6 +775,7 @@ void qmc_plan_destroy(qmc_plan_t p) {
     if (!p) return;
     if (p->stream) hipStreamSynchronize(p->stream);
     else hipDeviceSynchronize();
+    plan_release_extra(p);
     if (p->d_g) hipFree(p->d_g);
     if (p->d_gstep) hipFree(p->d_gstep);
     if (p->d_shifts) hipFree(p->d_shifts);
@@ -783,7 +784,6 @@ void qmc_plan_destroy(qmc_plan_t p) {
     if (p->h_out) hipHostFree(p->h_out);
     if (p->ev0) hipEventDestroy(p->ev0);
     if (p->ev1) hipEventDestroy(p->ev1);
-    plan_release_extra(p);
     delete p;
 }
 

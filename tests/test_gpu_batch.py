@@ -381,3 +381,25 @@ def test_specialised_graph_of_few_plans(Q, count):
         assert graph <= 4 / 3 * eager
     for p in plans:
         p.close()
+
+
+@pytest.mark.parametrize("schedule", ["specialised", "default"])
+def test_closed_plans_leave_no_graph(Q, schedule):
+    """Plans made after others were closed often lie at their addresses, with
+    buffers at theirs, and may have the same kernel and grid.  A graph captured
+    for the closed ones holds their lattice size: each set gets its own."""
+    m = 8
+    tabs = [synth.sector_tables(90 + i, 3 + i, 8, 20) for i in range(2)]
+    params = [Q.Params("sector", t.d, sector=t) for t in tabs]
+    for n in (16381, 16369, 16363, 16381, 16361, 15359):
+        plans = [Q.Plan(t.d, n, O.korobov_vector(n, t.d, 76), synth.shifts(i, m, t.d), "baker")
+                 for i, t in enumerate(tabs)]
+        _say(f"graph of new plans {schedule} n={n}")
+        got = Q.integrate_batch(plans, params, schedule=schedule)
+        for plan, p, r in zip(plans, params, got):
+            if schedule == "default":
+                plan.set_jit(0)
+            one, _ = plan.integrate(p)
+            assert _rel(r.mean_re, one.mean_re) < TOL and _rel(r.err_re, one.err_re) < 1e-5
+        for plan in plans:
+            plan.close()
